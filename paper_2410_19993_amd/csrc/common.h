@@ -357,6 +357,8 @@ hipError_t xbk_launch_factor(const xbk::GJArgs& a, bool fp32, hipStream_t s);
 hipError_t xbk_launch_ns_init(const xbk::NSArgs& a, hipStream_t s);
 hipError_t xbk_launch_ns_slots(const xbk::NSArgs& a, bool fp32, int chain, int first, int count, hipStream_t s);
 hipError_t xbk_launch_ns_finish(const xbk::NSArgs& a, int launched0, int launched1, int launched2, hipStream_t s);
+// whole factor of a plan with n_p = 64 (ns_chain.hip); report: a missed tolerance raises kErrConv
+hipError_t xbk_launch_ns_chains(const xbk::NSArgs& a, bool fp32, bool report, hipStream_t s);
 hipError_t xbk_launch_sweep(const xbk::SweepArgs& a, hipStream_t s);
 hipError_t xbk_launch_recover(const xbk::RecoverArgs& a, hipStream_t s);
 hipError_t xbk_launch_sweep_ir(const xbk::SweepArgs& a, hipStream_t s);

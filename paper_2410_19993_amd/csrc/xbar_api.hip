@@ -652,6 +652,28 @@ hipError_t run_ns(xbar_plan p, bool checked, bool* failed)
     return hipSuccess;
 }
 
+// Newton-Schulz factor of a plan whose row blocks fit one workgroup (n <= 64): two
+// launches at most, so there is no schedule to learn and nothing is read back, unless
+// the caller asked to know of a missed tolerance (checked).
+hipError_t run_ns_chains(xbar_plan p, bool checked, bool* failed)
+{
+    *failed = false;
+    hipError_t e = xbk_launch_ns_chains(ns_args(p), p->fp32(), !checked, p->stream);
+    if (e != hipSuccess) return e;
+    p->ns_launched[0] = p->g.m > 1 ? 1 : 0;
+    p->ns_launched[1] = 0;
+    p->ns_launched[2] = 1;
+    p->ns_used_host = p->ns_launched[0] + 1;
+    if (!checked) return hipSuccess;
+    int fail = 0;
+    if ((e = hipMemcpyAsync(&fail, p->d.flags + xbk::kNsFail, sizeof(int), hipMemcpyDeviceToHost, p->stream)) !=
+            hipSuccess ||
+        (e = hipStreamSynchronize(p->stream)) != hipSuccess)
+        return e;
+    *failed = fail != 0;
+    return hipSuccess;
+}
+
 __global__ void clear_flag_kernel(int* f, int which) { f[which] = 0; }
 
 // The bfloat16 trial: round every stored inverse block to the nearest bfloat16
@@ -786,10 +808,13 @@ xbar_status xbar_factor(xbar_plan p)
     } else {
         // AUTO reads the schedule back (and learns its launch counts) until it has
         // counts from an earlier factorization of this plan; then it runs asynchronously
-        const bool checked = p->factor_method != XBAR_FACTOR_AUTO || !p->ns_hint_valid;
-        p->ns_async = !checked;
+        const bool chains = p->n_p == 64;
+        const bool checked = chains ? p->factor_method == XBAR_FACTOR_CHECKED
+                                    : p->factor_method != XBAR_FACTOR_AUTO || !p->ns_hint_valid;
+        p->ns_async = !checked && !chains;
         bool failed = false;
-        if (run_ns(p, checked, &failed) != hipSuccess) return XBAR_ERR_DEVICE;
+        if ((chains ? run_ns_chains(p, checked, &failed) : run_ns(p, checked, &failed)) != hipSuccess)
+            return XBAR_ERR_DEVICE;
         if (failed && p->factor_method == XBAR_FACTOR_CHECKED) {
             // Redo the factorization by Gauss-Jordan elimination: rebuild E from the
             // plan's copy of G (the Newton-Schulz pass consumed part of it).

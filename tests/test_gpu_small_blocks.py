@@ -1,0 +1,45 @@
+"""Crossbars of at most 64 columns: the one-workgroup Newton-Schulz chains and the
+two-chain sweep, at the edges of their 16-column tiles, chain lengths and slabs.
+
+Against the CPU oracle with the float64 tolerance (1e-10: the gate of every float64
+solve) and the refinement's (1e-9); the currents-only sweep gives the same bits, and so
+does a vector solved alone.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from tests.gpu_util import TOL_FP64, TOL_IR, gpu_solve, log, node_rel_err, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 32, 33, 48, 49, 64])
+@pytest.mark.parametrize("m,B", [(1, 16), (2, 1), (3, 17), (4, 33), (11, 16), (12, 31)])
+def test_small_blocks_match_oracle(m, n, B):
+    wl = workloads.random_crossbar(m, n, B, 9000 + 64 * m + n, r_wl=1.5, r_bl=3.0, r_src=40.0, r_sense=60.0)
+    log(f"case {wl.name}")
+    ref = oracle.solve_workload(wl)
+    I, nv, (st, info) = gpu_solve(wl.G, wl.V, wl.geom, ordering="rows")
+    assert st == 0 and 0 < info.factor_slots_used <= info.factor_slots_launched
+    assert rel_err(I, ref.currents).max() <= TOL_FP64
+    assert node_rel_err(nv, ref.node_v).max() <= TOL_FP64
+    I2, _, _ = gpu_solve(wl.G, wl.V, wl.geom, node_voltages=False, ordering="rows")
+    assert np.array_equal(I, I2)
+    k = B - 1
+    Ik, nvk, _ = gpu_solve(wl.G, wl.V[k:k + 1], wl.geom, ordering="rows")
+    assert np.array_equal(Ik[0], I[k]) and np.array_equal(nvk[0], nv[k])
+    If, nvf, (st, _) = gpu_solve(wl.G, wl.V, wl.geom, "fp32_ir", ordering="rows")
+    assert st == 0
+    assert rel_err(If, ref.currents).max() <= TOL_IR and node_rel_err(nvf, ref.node_v).max() <= TOL_IR
+
+
+@pytest.mark.parametrize("m,n", [(3, 17), (20, 64)])
+def test_small_blocks_of_a_wide_crossbar(m, n):
+    """The same sweeps with the inputs on the terminations (reciprocal ordering)."""
+    wl = workloads.random_crossbar(m, n, 18, 9900 + n, r_wl=1.5, r_bl=3.0, r_src=40.0, r_sense=60.0)
+    ref = oracle.solve_workload(wl)
+    I, nv, (st, _) = gpu_solve(wl.G, wl.V, wl.geom, ordering="smaller")
+    assert st == 0
+    assert rel_err(I, ref.currents).max() <= TOL_FP64 and node_rel_err(nv, ref.node_v).max() <= TOL_FP64
