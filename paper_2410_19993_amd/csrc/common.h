@@ -360,6 +360,8 @@ hipError_t xbk_launch_ns_finish(const xbk::NSArgs& a, int launched0, int launche
 // whole factor of a plan with n_p = 64 (ns_chain.hip); report: a missed tolerance raises kErrConv
 hipError_t xbk_launch_ns_chains(const xbk::NSArgs& a, bool fp32, bool report, hipStream_t s);
 hipError_t xbk_launch_sweep(const xbk::SweepArgs& a, hipStream_t s);
+// float64 sweep of a plan (one crossbar): picks the kernels by block size and batch (sweep_rows.hip)
+hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s);
 hipError_t xbk_launch_recover(const xbk::RecoverArgs& a, hipStream_t s);
 hipError_t xbk_launch_sweep_ir(const xbk::SweepArgs& a, hipStream_t s);
 hipError_t xbk_launch_residual(const xbk::ResidualArgs& a, hipStream_t s);

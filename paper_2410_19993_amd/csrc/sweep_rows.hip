@@ -1,0 +1,321 @@
+// Forward and back substitution of a plan's batch where the slab sweep (sweep.hip: one
+// workgroup walks all the row blocks for 16 input vectors) leaves the GPU waiting:
+//
+//  * sweep_small_kernel, n <= 64: both chains of the twisted order in one workgroup.
+//    A row block is at most 4 x 4 tiles, so a step is a short dependent chain (LDS
+//    read, 4 LT matrix instructions, LDS write, barrier); the chains' steps run side by
+//    side and nothing is computed past the last live 16 x 16 tile.
+//  * recover_rows_kernel: the word lines and node voltages of every row at once, from
+//    the solution the sweep left in the workspace.
+//
+// The products, the order of their sums and the recovery are those of the slab sweep, so
+// an input vector's results have the same bits whichever kernel ran and whatever shares
+// its batch.
+#include "recover.h"
+
+namespace xbk {
+
+namespace {
+
+typedef double d2v __attribute__((ext_vector_type(2)));
+
+// A-operand fragment of an FRG tile.
+__device__ __forceinline__ d4_t frag_load(const double* __restrict__ tile, int l)
+{
+    const d2v lo = *reinterpret_cast<const d2v*>(tile + 2 * l);
+    const d2v hi = *reinterpret_cast<const d2v*>(tile + 128 + 2 * l);
+    return d4_t{lo[0], lo[1], hi[0], hi[1]};
+}
+__device__ __forceinline__ d4_t load4(const double* p)
+{
+    const d2v lo = *reinterpret_cast<const d2v*>(p), hi = *reinterpret_cast<const d2v*>(p + 2);
+    return d4_t{lo[0], lo[1], hi[0], hi[1]};
+}
+__device__ __forceinline__ void store4(double* p, d4_t v)
+{
+    *reinterpret_cast<d2v*>(p) = d2v{v[0], v[1]};
+    *reinterpret_cast<d2v*>(p + 2) = d2v{v[2], v[3]};
+}
+
+// ---------------------------------------------------------------------------
+// n <= 64 (n_p = 64), m >= 3.  Waves c LT + t: row tile t of chain c (0: rows from the
+// top, 1: from the bottom).  Forward step p < F = kt is row p and row m - 1 - (p - late):
+// the bottom chain is one row shorter when m is even, and then starts one step late
+// (from a zero panel, whose product adds nothing).  Both chains form the twist row's
+// product, each for the panel it continues from.  Back step s is row kt - s and row
+// kt + s (the late chain repeats u_kt in step 1), or without node voltages (UP = false)
+// the bottom chain alone: the output currents depend on u_{m-1} only.
+//
+// A step's panel goes to the other of two LDS buffers: one barrier a step.  H,
+// right-hand sides and forward results are requested D steps ahead, and every load is
+// unconditional (clamped rows), so that no step waits for a load it does not use: with
+// the loads behind branches and one step ahead, a step of 32 columns took 1.14 us.
+//
+// Bound: the latency of a step, 4 LT dependent matrix instructions of each chain between
+// an LDS write, a barrier and an LDS read, and at LT = 4 the 64 KB of H that a step
+// brings through one CU's L1.  Measured: 0.64 us a step at 32 columns (700 rows, 16
+// vectors: 448 us; the slab sweep 3932 us, whose one matrix-core wave walks both chains
+// in turn on padded blocks), 2.0 us at 50 columns (65 rows, 20 vectors: 132 us), 10 us
+// for 16 x 16 (99 us).
+template <int V> struct Slot { static constexpr int value = V; };
+
+template <int LT, bool UP>
+__global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
+{
+    constexpr int n_p = 64, ldy = 16 * LT + 4, D = 4;
+    __shared__ __align__(16) double pan[2][2][16 * ldy];       // [chain][buffer][vector][CPR position]
+    const int l = threadIdx.x & 63, q = l >> 4, col = l & 15;
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int c = w / LT, t = w % LT;
+    const int n = a.n, m = a.m, kt = m / 2, F = kt, late = kt - (m - 1 - kt);
+    const int last = F + (UP ? kt : m - 1 - kt), late_back = UP ? late : 0;
+    const int slab = blockIdx.x, b = 16 * slab + col;
+    const bool bval = b < a.B;
+    const double g = a.g_bl;
+    const double* const H = reinterpret_cast<const double*>(a.H) + (int64_t)t * (n_p >> 4) * 256;
+    double* const Z = reinterpret_cast<double*>(a.Z) + (int64_t)slab * m * 16 * n_p + col * n_p + 16 * t + 4 * q;
+    const double* const C = a.c + 16 * t + q;                  // zero on the padding
+    // input voltage of this lane's vector; reciprocal ordering: none (the terminations'
+    // right-hand side of the last row is set apart)
+    const bool src = bval && !a.term;
+    const double* const Vb = a.V + (src ? (int64_t)b * m : 0);
+    const int64_t blk = n_p * n_p, zrow = 16 * n_p;
+    const int at = col * ldy + 16 * t + 4 * q;                 // this lane's rows in a panel
+
+    auto row_of = [&](int p) {
+        p = min(p, last);
+        if (c == 0) return p <= F ? p : (UP ? kt - (p - F) : kt);
+        return p < F ? m - 1 - max(p - late, 0) : kt + max(p - F - late_back, 0);
+    };
+    // of step p, in slot p % D: the H tiles, and (rq, vq) the source coupling and input
+    // voltage of its row (forward) or its forward result (back)
+    d4_t ring[D][LT], rq[D];
+    double vq[D];
+    auto load_h = [&](int p, d4_t (&h)[LT]) {
+        const double* Hi = H + row_of(p) * blk;
+#pragma unroll
+        for (int k = 0; k < LT; ++k) h[k] = frag_load(Hi + k * 256, l);
+    };
+    // right-hand side V_i c_i of step p <= F, multiplied where it is used
+    auto load_rhs = [&](int p, d4_t& r, double& v) {
+        const int i = row_of(min(p, F));
+        v = Vb[src ? i : 0];
+        const double* ci = C + (int64_t)i * n_p;
+        r = d4_t{ci[0], ci[4], ci[8], ci[12]};
+    };
+    auto rhs = [&](const d4_t& r, double v) { return r * (src ? v : 0.0); };
+    auto load_z = [&](int p, d4_t& r) { r = load4(Z + row_of(p) * zrow); };
+    auto product = [&](const d4_t (&h)[LT], const double* y) {
+        d4_t acc{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int k = 0; k < LT; ++k) {
+            const d4_t yv = load4(y + col * ldy + 16 * k + 4 * q);
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc = Frag<double>::mma(h[k][s], yv[s], acc);
+        }
+        return acc;
+    };
+    auto axpy = [&](d4_t x, d4_t y) {                          // g x + y
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = __builtin_fma(g, x[v], y[v]);
+        return x;
+    };
+    auto rotate = [&]() {                                       // slot 0 becomes the next step's
+#pragma unroll
+        for (int k = 0; k < LT; ++k) {
+            const d4_t r0 = ring[0][k];
+#pragma unroll
+            for (int d = 0; d + 1 < D; ++d) ring[d][k] = ring[d + 1][k];
+            ring[D - 1][k] = r0;
+        }
+        const d4_t r0 = rq[0];
+        const double v0 = vq[0];
+#pragma unroll
+        for (int d = 0; d + 1 < D; ++d) {
+            rq[d] = rq[d + 1];
+            vq[d] = vq[d + 1];
+        }
+        rq[D - 1] = r0;
+        vq[D - 1] = v0;
+    };
+
+#pragma unroll
+    for (int d = 0; d < D; ++d) {
+        load_rhs(d, rq[d], vq[d]);
+        load_h(d, ring[d]);
+    }
+    // the first row's right-hand side: the first panel, or, for a chain that starts late,
+    // what step 0 adds to its zero product
+    d4_t f0 = rhs(rq[0], vq[0]);
+    if (a.term && c == 1) {
+        const double* Vt = a.V + (int64_t)(bval ? b : 0) * n + (n - 1);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int k = 16 * t + Frag<double>::drow(q, v);
+            const double x = Vt[-min(k, n - 1)];
+            f0[v] = (bval && k < n) ? a.g_sense * x : 0.0;
+        }
+    }
+    const bool idle = c == 1 && late == 1;
+    store4(&pan[c][0][at], idle ? d4_t{0.0, 0.0, 0.0, 0.0} : f0);
+    int cur = 0;
+    lds_barrier();
+
+    // forward, step p in ring slot d
+    auto forward = [&](int p, auto slot) {
+        constexpr int d = decltype(slot)::value;
+        const d4_t z = product(ring[d], pan[c][cur]);
+        store4(Z + row_of(p) * zrow, z);
+        d4_t f = rhs(rq[(d + 1) % D], vq[(d + 1) % D]);
+        if (p == 0 && idle) f = f0;
+        // the next row's panel, or the forward result itself for the twist
+        const d4_t y = axpy(z, f);
+        store4(&pan[c][cur ^ 1][at], p + 1 < F ? y : z);
+        load_h(p + D, ring[d]);
+        load_rhs(p + D, rq[d], vq[d]);
+        cur ^= 1;
+        lds_barrier();
+    };
+    int p = 0;
+    for (; p + D <= F; p += D) {
+        forward(p, Slot<0>{});
+        forward(p + 1, Slot<1>{});
+        forward(p + 2, Slot<2>{});
+        forward(p + 3, Slot<3>{});
+    }
+    for (; p < F; ++p) {
+        forward(p, Slot<0>{});
+        rotate();
+    }
+    // twist row
+    const d4_t ft = rhs(rq[0], vq[0]);
+#pragma unroll
+    for (int d = 0; d < D; ++d) load_z(F + max(d, 1), rq[d]);
+    const d4_t yt = axpy(load4(&pan[1][cur][at]), axpy(load4(&pan[0][cur][at]), ft));
+    store4(&pan[c][cur ^ 1][at], yt);
+    cur ^= 1;
+    lds_barrier();
+    const d4_t ut = product(ring[0], pan[c][cur]);
+    if (UP && c == 0) store4(Z + kt * zrow, ut);
+    store4(&pan[c][cur ^ 1][at], ut);
+    load_h(F + D, ring[0]);
+    load_z(F + D, rq[0]);
+    cur ^= 1;
+    lds_barrier();
+    rotate();
+    if (!UP && c == 0) {
+        for (p = F + 1; p <= last; ++p) lds_barrier();
+        return;
+    }
+    // back, step p in ring slot d
+    d4_t u = ut;
+    auto back = [&](int p, auto slot) {
+        constexpr int d = decltype(slot)::value;
+        u = axpy(product(ring[d], pan[c][cur]), rq[d]);
+        if (UP) {
+            if (idle && p == F + 1) u = ut;
+            store4(Z + row_of(p) * zrow, u);
+        }
+        store4(&pan[c][cur ^ 1][at], u);
+        load_h(p + D, ring[d]);
+        load_z(p + D, rq[d]);
+        cur ^= 1;
+        lds_barrier();
+    };
+    p = F + 1;
+    for (; p + D <= last + 1; p += D) {
+        back(p, Slot<0>{});
+        back(p + 1, Slot<1>{});
+        back(p + 2, Slot<2>{});
+        back(p + 3, Slot<3>{});
+    }
+    for (; p <= last; ++p) {
+        back(p, Slot<0>{});
+        rotate();
+    }
+    if (c == 1 && bval) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int k = 16 * t + Frag<double>::drow(q, v);
+            if (k < n) a.Iout[(int64_t)b * n + k] = a.g_sense * u[v];
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// Word lines and node voltages of row i for the vectors of a slab, one workgroup each:
+// blockIdx.x = slab m + i, kHelpers waves of four vectors.  Bound: HBM (u read, 2 x
+// node voltages written) once enough rows are in flight; one row alone is the latency
+// of its segmented scans (5.2 us for 16 x 16 with 8 vectors, 9.6 us for 700 x 32 with 16).
+template <int NT>
+__global__ __launch_bounds__(64 * kHelpers) void recover_rows_kernel(SweepArgs a)
+{
+    using R = RowRecover<double, NT>;
+    constexpr int n_p = R::n_p, ldy = R::ldy;
+    extern __shared__ __align__(16) double lds[];
+    const int n = a.n, m = a.m;
+    const int slab = blockIdx.x / m, i = blockIdx.x % m;
+    const int lg = seg_lg(n, R::LR), PL = padded_len(n, R::LR);
+    double* ybuf = lds;                       // [16][ldy]
+    double* wv = ybuf + 16 * ldy;             // [16][PL]
+    double* coef = wv + 16 * PL;              // [3][PL] fr, ip, G of the row
+    const double* U = reinterpret_cast<const double*>(a.Z) + ((int64_t)slab * m + i) * 16 * n_p;
+    const int l = threadIdx.x & 63, h = threadIdx.x >> 6;
+    const int vecs = min(16, a.B - 16 * slab), used = (n + 15) & ~15;
+    // wave h copies the vectors it recovers
+    for (int v = h * R::VPW; v < min(vecs, (h + 1) * R::VPW); ++v)
+        for (int k = 2 * l; k < used; k += 128)
+            *reinterpret_cast<d2v*>(ybuf + v * ldy + k) = *reinterpret_cast<const d2v*>(U + (int64_t)v * n_p + k);
+    for (int j = threadIdx.x; j < n; j += 64 * kHelpers) {
+        const int pj = padj(j, lg);
+        const int64_t o = (int64_t)i * n + j;
+        coef[pj] = a.fr[o];
+        coef[PL + pj] = a.ip[o];
+        coef[2 * PL + pj] = a.Gc[o];
+    }
+    const int bb = 16 * slab + h * R::VPW + l / R::LR;
+    const double vb = (bb < a.B && !a.term) ? a.V[(int64_t)bb * m + i] : 0.0;
+    __syncthreads();
+    if (h * R::VPW < vecs) R::run(a, slab, i, vb, ybuf, wv, coef, h, l, lg, PL);
+}
+
+template <int NT>
+hipError_t launch_recover_rows(const SweepArgs& a, hipStream_t s)
+{
+    using R = RowRecover<double, NT>;
+    const int64_t blocks = (int64_t)a.m * a.nslab;
+    if (blocks > INT32_MAX) return hipErrorInvalidValue;
+    const size_t lds = (16 * (size_t)R::ldy + 19 * (size_t)padded_len(a.n, R::LR)) * sizeof(double);
+    hipLaunchKernelGGL((recover_rows_kernel<NT>), dim3((unsigned)blocks), dim3(64 * kHelpers), lds, s, a);
+    return hipGetLastError();
+}
+
+template <int LT>
+hipError_t launch_small(const SweepArgs& a, hipStream_t s)
+{
+    if (a.node_v)
+        hipLaunchKernelGGL((sweep_small_kernel<LT, true>), dim3(a.nslab), dim3(128 * LT), 0, s, a);
+    else
+        hipLaunchKernelGGL((sweep_small_kernel<LT, false>), dim3(a.nslab), dim3(128 * LT), 0, s, a);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+}  // namespace xbk
+
+hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s)
+{
+    if (a.batch > 1 || a.unit) return hipErrorInvalidValue;
+    // (one or two rows have no chains to run side by side)
+    if (a.n_p != 64 || a.m < 3 || (int64_t)a.m * a.nslab > INT32_MAX) return xbk_launch_sweep(a, s);
+    hipError_t e = hipErrorInvalidValue;
+    switch ((a.n + 15) / 16) {
+        case 1: e = xbk::launch_small<1>(a, s); break;
+        case 2: e = xbk::launch_small<2>(a, s); break;
+        case 3: e = xbk::launch_small<3>(a, s); break;
+        case 4: e = xbk::launch_small<4>(a, s); break;
+    }
+    if (e != hipSuccess || !a.node_v) return e;
+    return xbk::launch_recover_rows<1>(a, s);
+}

@@ -955,7 +955,7 @@ xbar_status xbar_solve_batch(xbar_plan p, const double* V, int32_t B, double* no
     s.g_wl = 1.0 / p->g.r_wl;
     if (p->timing && !p->t_sweep.begin(p->stream)) return XBAR_ERR_DEVICE;
     if (!ir) {
-        if (xbk_launch_sweep(s, p->stream) != hipSuccess) return XBAR_ERR_DEVICE;
+        if (xbk_launch_sweep_plan(s, p->stream) != hipSuccess) return XBAR_ERR_DEVICE;
     } else {
         // float sweeps refined in float64: sweep 0 solves with V c, each later sweep
         // corrects U by the solution for the float64 residual of the previous U.
