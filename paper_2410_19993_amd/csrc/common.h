@@ -290,6 +290,7 @@ struct SweepArgs {
     // m-1, so the right-hand side is g_sense V[b][n-1-k] at row m-1 and zero elsewhere,
     // and the word lines have no sources
     int term = 0;
+    double* ysteps = nullptr;        // step path: [2 chains][2][nslab][16][n_p] right-hand side panels
 };
 
 struct ResidualArgs {
@@ -360,8 +361,10 @@ hipError_t xbk_launch_ns_finish(const xbk::NSArgs& a, int launched0, int launche
 // whole factor of a plan with n_p = 64 (ns_chain.hip); report: a missed tolerance raises kErrConv
 hipError_t xbk_launch_ns_chains(const xbk::NSArgs& a, bool fp32, bool report, hipStream_t s);
 hipError_t xbk_launch_sweep(const xbk::SweepArgs& a, hipStream_t s);
+hipError_t xbk_launch_sweep_parts(const xbk::SweepArgs& a, hipStream_t s);   // one chain per workgroup, n_p > 64
 // float64 sweep of a plan (one crossbar): picks the kernels by block size and batch (sweep_rows.hip)
 hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s);
+int xbk_step_slabs(int n_p);        // slabs up to which it runs step by step over the GPU
 hipError_t xbk_launch_recover(const xbk::RecoverArgs& a, hipStream_t s);
 hipError_t xbk_launch_sweep_ir(const xbk::SweepArgs& a, hipStream_t s);
 hipError_t xbk_launch_residual(const xbk::ResidualArgs& a, hipStream_t s);

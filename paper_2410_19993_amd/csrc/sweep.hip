@@ -448,6 +448,23 @@ struct SweepPlan {
     }
 };
 
+// Schedule of one chain's part of a split sweep (rows first, first + dir, ..., count of
+// them): forward, a pair before each row's product; back, the twist row's pair first,
+// then a pair after each solution row, from u_kt on.
+struct PartPlan {
+    int kt, first, dir, count;
+    bool back, own_kt;             // own_kt: this chain's helpers recover row kt
+    __device__ __forceinline__ int pairs() const { return back ? 2 + count : count; }
+    __device__ __forceinline__ int product_after(int p) const {
+        if (!back) return p < count ? first + dir * p : -1;
+        return p == 0 ? kt : p <= count ? first + dir * (p - 1) : -1;
+    }
+    __device__ __forceinline__ int recover_after(int p) const {
+        if (!back || p < 1 || (p == 1 && !own_kt)) return -1;
+        return p == 1 ? kt : first + dir * (p - 2);
+    }
+};
+
 // Helper waves of the float64 sweep.  While the matrix-core waves run the product
 // that follows a barrier pair, the helpers
 //  * pull this workgroup's share of the next row's H block into L2 (workgroups b,
@@ -507,9 +524,9 @@ struct SweepHelper {
     __device__ __forceinline__ void recover(int i, int buf) {
         RowRecover<T, NT>::run(a, a.slab, i, vcur, ybuf, wv, coef + buf * 3 * PL, h, l, lg, PL);
     }
-    // the whole schedule, one barrier pair at a time
-    __device__ void run(bool rec, bool up) {
-        const SweepPlan sp(a.m, up);
+    // the whole schedule sp, one barrier pair at a time
+    template <typename Plan>
+    __device__ __forceinline__ void run(const Plan& sp, bool rec) {
         const int np = sp.pairs();
         const T* H = reinterpret_cast<const T*>(a.H);
         for (int p = 0; p < np; ++p) {
@@ -592,7 +609,7 @@ __global__ __launch_bounds__(64 * (SweepWaves<NT>::value + SweepHelpers<IR>::val
             // the helpers' latency-bound work gets issue priority over the matrix-core
             // waves, which have independent work queued behind every instruction
             __builtin_amdgcn_s_setprio(3);
-            hp.run(REC, REC);
+            hp.run(SweepPlan(a.m, REC), REC);
             return;
         }
     }
@@ -691,6 +708,82 @@ __global__ __launch_bounds__(64 * (SweepWaves<NT>::value + SweepHelpers<IR>::val
     }
     if (IR && a.tol >= 0.0) x.decide(extra);
     if constexpr (NH == 0) pull.retire(a, l);
+}
+
+// The float64 sweep of one chain per workgroup, for batches of at most half as many slabs
+// as there are CUs: a launch for the forward halves, one for the back halves (which start
+// from the twist row; both chains form its product).  m >= 3; the products, sums and
+// recovery of sweep_kernel, on 2 nslab workgroups with half the rows each.  Workgroups
+// b % 8 < 4 (four XCDs) take the top chain, the others the bottom chain, so that an
+// XCD's workgroups read the same H blocks.  Without node voltages the back launch has
+// the bottom chain only.
+template <int NT, bool BACK, bool REC>
+__global__ __launch_bounds__(64 * (SweepWaves<NT>::value + kHelpers)) void sweep_part_kernel(SweepArgs a)
+{
+    constexpr int W = SweepWaves<NT>::value, DP = kRing;
+    extern __shared__ __align__(32) unsigned char smem_raw[];
+    using Ctx = SweepCtx<double, NT, false, W>;
+    using acc_t = typename Ctx::acc_t;
+    constexpr int TW = Ctx::TW;
+    constexpr bool both = !BACK || REC;
+    const int chain = both ? (blockIdx.x >> 2) & 1 : 1;
+    a.slab = both ? (int)(blockIdx.x >> 3) * 4 + (int)(blockIdx.x & 3) : (int)blockIdx.x;
+    if (a.slab >= a.nslab) return;
+    const int m = a.m, kt = m / 2;
+    const int dir = (chain == 0) != BACK ? 1 : -1;
+    const int first = BACK ? kt + dir : (chain == 0 ? 0 : m - 1);
+    const int count = chain == 0 ? kt : m - 1 - kt;
+    const int l = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    double* extra = reinterpret_cast<double*>(smem_raw + 16 * Ctx::ldy * sizeof(double));
+    if (wave >= W) {
+        const int PL = padded_len(a.n, SweepHelper<double, NT>::LR);
+        SweepHelper<double, NT> hp{a, reinterpret_cast<const double*>(smem_raw), extra, wave - W, l,
+                                   seg_lg(a.n, SweepHelper<double, NT>::LR), PL};
+        hp.coef = extra + 16 * PL;
+        __builtin_amdgcn_s_setprio(3);
+        hp.run(PartPlan{kt, first, dir, count, BACK, chain == 0}, BACK && REC);
+        return;
+    }
+    Ctx x{a, reinterpret_cast<double*>(smem_raw),
+          reinterpret_cast<double*>(a.Z) + (int64_t)a.slab * m * 16 * Ctx::n_p,
+          reinterpret_cast<const double*>(a.H), wave, l, l >> 4, l & 15,
+          16 * a.slab + (l & 15), false, a.g_bl};
+    x.bval = x.b < a.B;
+    const int64_t blk = (int64_t)Ctx::n_p * Ctx::n_p;
+    auto Hb = [&](int i) { return x.H + i * blk; };
+    acc_t acc[TW];
+    const NoHook none{};
+    HRing<double, NT, TW, DP> ring;
+    ring.prime(Hb(BACK ? kt : first), x.w, l);
+    auto product = [&](acc_t (&out)[TW], int i, int nx) {
+        panel_product<double, NT, TW>(out, ring, Hb(i), Hb(nx), x.ybuf, Ctx::ldy, x.w, l, none);
+    };
+    double f[TW][4];
+    if (!BACK) {
+        x.load_rhs(first, f);
+        x.set_panel(f, acc, false, -1, -1);
+        for (int k = 0; k < count; ++k) {
+            const int i = first + dir * k;
+            if (k + 1 < count) x.template load_rhs<false>(i + dir, f);
+            product(acc, i, k + 1 < count ? i + dir : i);
+            x.store_z(i, acc);
+            if (k + 1 < count) x.set_panel(f, acc, true, -1, -1);
+        }
+        return;
+    }
+    x.load_rhs(kt, f);
+    x.set_panel(f, acc, false, kt - 1, kt + 1);
+    product(acc, kt, first);
+    x.put_panel(acc);
+    for (int k = 0; k < count; ++k) {
+        const int i = first + dir * k;
+        product(acc, i, k + 1 < count ? i + dir : i);
+        x.load_z(i, f);
+        x.back_step(f, acc);
+        if (i == m - 1) x.currents(acc);
+        x.put_panel(acc);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -991,6 +1084,22 @@ hipError_t launch_sweep_nt(const SweepArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+template <int NT>
+hipError_t launch_sweep_parts(const SweepArgs& a, hipStream_t s)
+{
+    constexpr int threads = 64 * (SweepWaves<NT>::value + kHelpers);
+    const size_t lds = sweep_lds_bytes<double, NT, false>(a.n);
+    const unsigned both = (unsigned)((a.nslab + 3) / 4 * 8);
+    hipLaunchKernelGGL((sweep_part_kernel<NT, false, false>), dim3(both), dim3(threads), lds, s, a);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    if (a.node_v != nullptr)
+        hipLaunchKernelGGL((sweep_part_kernel<NT, true, true>), dim3(both), dim3(threads), lds, s, a);
+    else
+        hipLaunchKernelGGL((sweep_part_kernel<NT, true, false>), dim3(a.nslab), dim3(threads), lds, s, a);
+    return hipGetLastError();
+}
+
 template <typename T, bool IR>
 hipError_t launch_sweep(const SweepArgs& a, hipStream_t s)
 {
@@ -1012,6 +1121,21 @@ hipError_t launch_sweep(const SweepArgs& a, hipStream_t s)
 hipError_t xbk_launch_sweep(const xbk::SweepArgs& a, hipStream_t s)
 {
     return xbk::launch_sweep<double, false>(a, s);
+}
+
+hipError_t xbk_launch_sweep_parts(const xbk::SweepArgs& a, hipStream_t s)
+{
+    if (a.m < 3 || a.batch > 1 || a.unit) return hipErrorInvalidValue;
+    switch (a.n_p / 64) {
+        case 2: return xbk::launch_sweep_parts<2>(a, s);
+        case 3: return xbk::launch_sweep_parts<3>(a, s);
+        case 4: return xbk::launch_sweep_parts<4>(a, s);
+        case 5: return xbk::launch_sweep_parts<5>(a, s);
+        case 6: return xbk::launch_sweep_parts<6>(a, s);
+        case 7: return xbk::launch_sweep_parts<7>(a, s);
+        case 8: return xbk::launch_sweep_parts<8>(a, s);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t xbk_launch_sweep_ir(const xbk::SweepArgs& a, hipStream_t s)

@@ -5,12 +5,17 @@
 //    A row block is at most 4 x 4 tiles, so a step is a short dependent chain (LDS
 //    read, 4 LT matrix instructions, LDS write, barrier); the chains' steps run side by
 //    side and nothing is computed past the last live 16 x 16 tile.
+//  * sweep_step_kernel, larger n and batches that leave most CUs idle: one launch per
+//    step of the two chains, a row block's product spread over the GPU (a few row tiles
+//    and slabs per workgroup).
 //  * recover_rows_kernel: the word lines and node voltages of every row at once, from
 //    the solution the sweep left in the workspace.
 //
 // The products, the order of their sums and the recovery are those of the slab sweep, so
 // an input vector's results have the same bits whichever kernel ran and whatever shares
 // its batch.
+#include <algorithm>
+
 #include "recover.h"
 
 namespace xbk {
@@ -290,6 +295,212 @@ hipError_t launch_recover_rows(const SweepArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------
+// One step of both chains as a launch: H_row (its row tiles over the GPU) times the
+// panels of every slab.  Forward: z = H y, stored, and the next row's right-hand side
+// panel y' = f + g z.  Twist and back: u = H y, u = z + g H u', stored over z.
+//
+// Bound: few vectors, the start of a launch and one wave's chain of n_p / 4 dependent
+// matrix instructions (K is not split: the sums keep the slab sweep's order); more, the
+// L2-to-L1 rate.  Measured a step (two rows) with one vector: 5.0 us at n_p = 256, 5.7 at
+// 320, 8.4 at 512, against 21, 35 and 70 us on one workgroup; 512 vectors at 512: 23.5
+// against 72 us.
+// Slabs up to which the steps are launches over the GPU (n_p > 128), and up to which each
+// chain has workgroups of its own.  Microseconds a step with node voltages, as launches /
+// chain per workgroup / slab per workgroup, 768 vectors: n = 512 33 / 37 / 72, n = 256
+// 12.1 / 11.6 / 22; 1024 vectors: 512 42 / 37 / 72, 320 23 / 18 / 36, 192 10.6 / 9.2 / 18;
+// 512 vectors: 23.5 / 37, 14 / 18.5, 7.4 / 9.2.  At n_p = 128 a step is too short to be a
+// launch (4.6 / 3.7 / 7.4 with one vector).
+constexpr int kStepSlabs = 48, kPartSlabs = 128;
+
+struct StepJob {
+    int row = -1;          // row whose product this is (-1: none)
+    int next = -1;         // forward: row whose right-hand side panel follows (-1: none)
+    const double* pan = nullptr;   // panel of slab 0: [16][n_p], CPR
+    double* ynext = nullptr;       // forward: next panel of slab 0
+};
+struct StepArgs {
+    SweepArgs a;
+    StepJob job[2];
+    int64_t pan_stride;    // elements between the panels of consecutive slabs
+    int back;              // 0: forward or twist (u = H y), 1: u = z + g H u'
+};
+
+// Panels of the first rows (ra = rb = -1) or of the twist row, y = f + g z_ra + g z_rb.
+__global__ void step_form_kernel(SweepArgs a, int row0, double* y0, int row1, double* y1, int ra, int rb)
+{
+    const int n_p = a.n_p, m = a.m, n = a.n;
+    const int64_t panel = (int64_t)16 * n_p, total = panel * a.nslab;
+    const int i = blockIdx.y == 0 ? row0 : row1;
+    double* y = blockIdx.y == 0 ? y0 : y1;
+    for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t slab = e / panel, o = e - slab * panel;
+        const int p = (int)(o % n_p), b = (int)(16 * slab + o / n_p);
+        const int k = (p & ~15) + ((p & 15) >> 2) + 4 * (p & 3);             // CPR position -> k
+        const bool bval = b < a.B;
+        double f = 0.0;
+        if (a.term) {
+            if (i == m - 1 && bval && k < n) f = a.g_sense * a.V[(int64_t)b * n + (n - 1 - k)];
+        } else if (bval) {
+            f = a.c[(int64_t)i * n_p + k] * a.V[(int64_t)b * m + i];
+        }
+        const double* Zs = reinterpret_cast<const double*>(a.Z) + slab * m * panel + o;
+        if (ra >= 0) f = __builtin_fma(a.g_bl, Zs[ra * panel], f);
+        if (rb >= 0) f = __builtin_fma(a.g_bl, Zs[rb * panel], f);
+        y[e] = f;
+    }
+}
+
+// One wave a workgroup: row tile idx % KC, S slabs.  Workgroup b runs on XCD b % 8: with
+// two jobs each chain has four XCDs, and consecutive workgroups of an XCD group take
+// consecutive row tiles, so an XCD's L2 holds a quarter of each H block.
+template <int NT, int S>
+__global__ __launch_bounds__(64) void sweep_step_kernel(StepArgs sa)
+{
+    constexpr int n_p = 64 * NT, KC = 4 * NT;
+    constexpr int PF = S == 1 ? 12 : 6;                    // chunks in flight
+    const SweepArgs& a = sa.a;
+    const bool two = sa.job[1].row >= 0 && sa.job[0].row >= 0;
+    const int xcd = blockIdx.x & 7, local = blockIdx.x >> 3;
+    const int c = two ? xcd >> 2 : (sa.job[0].row >= 0 ? 0 : 1);
+    const int idx = two ? local * 4 + (xcd & 3) : blockIdx.x;
+    const int t = idx % KC, slab0 = (idx / KC) * S;
+    if (slab0 >= a.nslab) return;
+    const int row = c == 0 ? sa.job[0].row : sa.job[1].row;
+    const int next = c == 0 ? sa.job[0].next : sa.job[1].next;
+    const double* const pan = c == 0 ? sa.job[0].pan : sa.job[1].pan;
+    double* const ynext = c == 0 ? sa.job[0].ynext : sa.job[1].ynext;
+    const int l = threadIdx.x & 63, q = l >> 4, col = l & 15;
+    const int m = a.m, n = a.n;
+    const double* const H = reinterpret_cast<const double*>(a.H) + (int64_t)row * n_p * n_p + (int64_t)t * KC * 256;
+    const int last = a.nslab - 1;                          // slabs past the last repeat it, unstored
+    const double* y[S];
+#pragma unroll
+    for (int s = 0; s < S; ++s)
+        y[s] = pan + min(slab0 + s, last) * sa.pan_stride + col * n_p + 4 * q;
+    d4_t hr[PF], yr[PF][S], acc[S];
+#pragma unroll
+    for (int k = 0; k < PF; ++k) {
+        hr[k] = frag_load(H + k * 256, l);
+#pragma unroll
+        for (int s = 0; s < S; ++s) yr[k][s] = load4(y[s] + 16 * k);
+    }
+    // requested before the product, used after it
+    const int o = col * n_p + 16 * t + 4 * q;
+    double* const Z = reinterpret_cast<double*>(a.Z) + (int64_t)row * 16 * n_p + o;
+    const int64_t zslab = (int64_t)m * 16 * n_p;
+    const bool fwd = next >= 0;
+    d4_t e[S], cn{0.0, 0.0, 0.0, 0.0};
+    if (sa.back) {
+#pragma unroll
+        for (int s = 0; s < S; ++s) e[s] = load4(Z + min(slab0 + s, last) * zslab);
+    } else {
+        const double* ci = a.c + (int64_t)(fwd ? next : 0) * n_p + 16 * t + q;
+        cn = d4_t{ci[0], ci[4], ci[8], ci[12]};
+#pragma unroll
+        for (int s = 0; s < S; ++s) {
+            const int b = 16 * (slab0 + s) + col;
+            const bool src = fwd && b < a.B && !a.term;
+            const double v = a.V[src ? (int64_t)b * m + next : 0];
+            e[s] = d4_t{src ? v : 0.0, 0.0, 0.0, 0.0};
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) acc[s] = d4_t{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int k = 0; k < KC; ++k) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+            for (int s = 0; s < S; ++s) acc[s] = Frag<double>::mma(hr[k % PF][j], yr[k % PF][s][j], acc[s]);
+        if (k + PF < KC) {
+            hr[k % PF] = frag_load(H + (k + PF) * 256, l);
+#pragma unroll
+            for (int s = 0; s < S; ++s) yr[k % PF][s] = load4(y[s] + 16 * (k + PF));
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        const int slab = slab0 + s;
+        if (slab > last) break;
+        d4_t u = acc[s];
+        if (sa.back) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) u[v] = __builtin_fma(a.g_bl, u[v], e[s][v]);
+        }
+        store4(Z + slab * zslab, u);
+        if (fwd) {
+            const d4_t f = cn * e[s][0];
+            d4_t yn;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) yn[v] = __builtin_fma(a.g_bl, u[v], f[v]);
+            store4(ynext + (int64_t)slab * 16 * n_p + o, yn);
+        }
+        // the last row's solution: a back step's, or the twist's when it is the last row
+        if (row == m - 1 && (sa.back || m - 1 == m / 2)) {
+            const int b = 16 * slab + col;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = 16 * t + Frag<double>::drow(q, v);
+                if (b < a.B && k < n) a.Iout[(int64_t)b * n + k] = a.g_sense * u[v];
+            }
+        }
+    }
+}
+
+template <int NT, int S>
+hipError_t launch_step(const StepArgs& sa, hipStream_t s)
+{
+    const int work = 4 * NT * ((sa.a.nslab + S - 1) / S);
+    const bool two = sa.job[0].row >= 0 && sa.job[1].row >= 0;
+    hipLaunchKernelGGL((sweep_step_kernel<NT, S>), dim3(two ? 8 * ((work + 3) / 4) : work), dim3(64), 0, s, sa);
+    return hipGetLastError();
+}
+
+template <int NT, int S>
+hipError_t run_steps(const SweepArgs& a, hipStream_t s)
+{
+    const int m = a.m, kt = m / 2;
+    const int64_t row = (int64_t)16 * a.n_p, panel = row * a.nslab;
+    double* const Y = a.ysteps;                            // [2 chains][2][nslab][16][n_p]
+    double* const Z = reinterpret_cast<double*>(a.Z);
+    const unsigned blocks = (unsigned)std::min<int64_t>((panel + 255) / 256, 2048);
+    const bool bottom = kt + 1 < m;
+    StepArgs sa;
+    sa.a = a;
+    hipError_t e = hipSuccess;
+    if (kt > 0) {
+        hipLaunchKernelGGL(step_form_kernel, dim3(blocks, bottom ? 2 : 1), dim3(256), 0, s, a, 0, Y, m - 1,
+                           Y + 2 * panel, -1, -1);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+    }
+    sa.pan_stride = row;
+    sa.back = 0;
+    for (int p = 0; p < kt; ++p) {
+        const int rows[2] = {p, m - 1 - p > kt ? m - 1 - p : -1};
+        const int next[2] = {p + 1 < kt ? p + 1 : -1, m - 2 - p > kt ? m - 2 - p : -1};
+        for (int c = 0; c < 2; ++c)
+            sa.job[c] = StepJob{rows[c], next[c], Y + (2 * c + (p & 1)) * panel, Y + (2 * c + ((p + 1) & 1)) * panel};
+        if ((e = launch_step<NT, S>(sa, s)) != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(step_form_kernel, dim3(blocks), dim3(256), 0, s, a, kt, Y, 0, nullptr, kt > 0 ? kt - 1 : -1,
+                       bottom ? kt + 1 : -1);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    sa.job[0] = StepJob{kt, -1, Y, nullptr};
+    sa.job[1] = StepJob{};
+    if ((e = launch_step<NT, S>(sa, s)) != hipSuccess) return e;
+    sa.pan_stride = m * row;
+    sa.back = 1;
+    for (int p = 1; p <= kt; ++p) {
+        // without node voltages only the rows below the twist (the currents' row is the last)
+        sa.job[0] = a.node_v ? StepJob{kt - p, -1, Z + (kt - p + 1) * row, nullptr} : StepJob{};
+        sa.job[1] = kt + p < m ? StepJob{kt + p, -1, Z + (kt + p - 1) * row, nullptr} : StepJob{};
+        if (sa.job[0].row < 0 && sa.job[1].row < 0) break;
+        if ((e = launch_step<NT, S>(sa, s)) != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 template <int LT>
 hipError_t launch_small(const SweepArgs& a, hipStream_t s)
 {
@@ -300,22 +511,53 @@ hipError_t launch_small(const SweepArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
+// One slab a wave up to a wave per SIMD, two (on each H tile it loads) past that: at
+// 512 x 512, 512 vectors, 23.5 against 24.7 us a step, at 16 vectors 10.7 against 8.4.
+// (Four row tiles a workgroup, so that they share the panels in its L1, and four slabs a
+// wave were slower at every size: 9.1 to 34 us at 16 vectors.)
+template <int NT>
+hipError_t run_steps_nt(const SweepArgs& a, hipStream_t s)
+{
+    const int waves = 2 * (4 * NT) * a.nslab;
+    const hipError_t e = waves <= 1024 ? run_steps<NT, 1>(a, s) : run_steps<NT, 2>(a, s);
+    if (e != hipSuccess || !a.node_v) return e;
+    return launch_recover_rows<NT>(a, s);
+}
+
 }  // namespace
 
 }  // namespace xbk
 
+int xbk_step_slabs(int n_p)
+{
+    return n_p > 128 ? xbk::kStepSlabs : 0;
+}
+
 hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s)
 {
     if (a.batch > 1 || a.unit) return hipErrorInvalidValue;
-    // (one or two rows have no chains to run side by side)
-    if (a.n_p != 64 || a.m < 3 || (int64_t)a.m * a.nslab > INT32_MAX) return xbk_launch_sweep(a, s);
-    hipError_t e = hipErrorInvalidValue;
-    switch ((a.n + 15) / 16) {
-        case 1: e = xbk::launch_small<1>(a, s); break;
-        case 2: e = xbk::launch_small<2>(a, s); break;
-        case 3: e = xbk::launch_small<3>(a, s); break;
-        case 4: e = xbk::launch_small<4>(a, s); break;
+    // one or two rows have no chains to run side by side
+    if (a.m < 3 || (int64_t)a.m * a.nslab > INT32_MAX) return xbk_launch_sweep(a, s);
+    if (a.n_p == 64) {
+        hipError_t e = hipErrorInvalidValue;
+        switch ((a.n + 15) / 16) {
+            case 1: e = xbk::launch_small<1>(a, s); break;
+            case 2: e = xbk::launch_small<2>(a, s); break;
+            case 3: e = xbk::launch_small<3>(a, s); break;
+            case 4: e = xbk::launch_small<4>(a, s); break;
+        }
+        if (e != hipSuccess || !a.node_v) return e;
+        return xbk::launch_recover_rows<1>(a, s);
     }
-    if (e != hipSuccess || !a.node_v) return e;
-    return xbk::launch_recover_rows<1>(a, s);
+    if (a.nslab > xbk::kPartSlabs) return xbk_launch_sweep(a, s);
+    if (a.ysteps == nullptr || a.nslab > xbk_step_slabs(a.n_p)) return xbk_launch_sweep_parts(a, s);
+    switch (a.n_p / 64) {
+        case 3: return xbk::run_steps_nt<3>(a, s);
+        case 4: return xbk::run_steps_nt<4>(a, s);
+        case 5: return xbk::run_steps_nt<5>(a, s);
+        case 6: return xbk::run_steps_nt<6>(a, s);
+        case 7: return xbk::run_steps_nt<7>(a, s);
+        case 8: return xbk::run_steps_nt<8>(a, s);
+        default: return hipErrorInvalidValue;
+    }
 }

@@ -30,6 +30,7 @@ struct Buffers {
     double* Iout = nullptr;   // [max_batch][n]
     int* flags = nullptr;     // [kNumFlags]
     unsigned long long* diag = nullptr;   // [kNumDiag]: smallest pivot key, largest backward error bits
+    double* ysteps = nullptr; // [2 chains][2][slabs][16][n_p]: panels of the step path
     double* sink = nullptr;   // [128]: target of the sweep's L2-pull keep-alive store
     // Newton-Schulz factor: per chain S, X[2], Q ([n_p][n_p]) and dprev ([2][n_p])
     void* ns_S[2] = {nullptr, nullptr};
@@ -178,7 +179,7 @@ void free_all(xbar_plan p)
 {
     Buffers& d = p->d;
     void* all[] = {d.H, d.c, d.fr, d.ip, d.q, d.Gc, d.S[0][0], d.S[0][1], d.S[1][0], d.S[1][1],
-                   d.P[0][0], d.P[0][1], d.P[1][0], d.P[1][1], d.Z, d.Iout, d.flags, d.diag, d.sink,
+                   d.P[0][0], d.P[0][1], d.P[1][0], d.P[1][1], d.Z, d.Iout, d.flags, d.diag, d.sink, d.ysteps,
                    d.ns_S[0], d.ns_S[1], d.ns_X[0][0], d.ns_X[0][1], d.ns_X[1][0], d.ns_X[1][1],
                    d.ns_Q[0], d.ns_Q[1],
                    d.ns_dprev[0], d.ns_dprev[1], d.ns_part, d.ns_state,
@@ -393,6 +394,8 @@ xbar_status xbar_create_ordered(const xbar_geometry* geom, xbar_precision prec, 
     }
     A((void**)&d.ns_part, 2 * (n_p / 32) * (n_p / 32) * 8);
     A((void**)&d.ns_state, 6 * sizeof(xbk::NSState));
+    if (prec == XBAR_FP64 && xbk_step_slabs(p->n_p) > 0)
+        A((void**)&d.ysteps, 4 * (int64_t)std::min(p->nslab_max, xbk_step_slabs(p->n_p)) * 16 * n_p * 8);
     if (!transfer_blocks_fit(p)) A((void**)&d.Vunit, (int64_t)p->tr_rows * og.m * 8);
     if (rev) {
         A((void**)&d.Grev, m * n * 8);
@@ -942,6 +945,7 @@ xbar_status xbar_solve_batch(xbar_plan p, const double* V, int32_t B, double* no
     s.Iout = p->d.Iout;
     s.flags = p->d.flags;
     s.sink = p->d.sink;
+    s.ysteps = p->d.ysteps;
     const bool ir = p->prec != XBAR_FP64;
     // reciprocal ordering: the inputs drive the terminations, and the node voltages are
     // always recovered (into the plan's buffer) for the given crossbar's currents

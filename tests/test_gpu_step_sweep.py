@@ -1,0 +1,53 @@
+"""Substitution as one launch per step of the two chains (more than 64 columns, batches
+that leave most of the GPU idle in the slab sweep), at every block size and choice of
+waves and slabs per workgroup, chain lengths of one to a few rows, and partial slabs.
+
+Against the CPU oracle within the float64 tolerance (1e-10: the gate of every float64
+solve), and bit for bit against the slab sweep, which a batch too large for the step path
+takes: an input vector's results do not depend on what shares its batch.
+"""
+import numpy as np
+import pytest
+
+import oracle
+import workloads
+from tests.gpu_util import TOL_FP64, gpu_solve, log, node_rel_err, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("m,n,B,seed", [
+    (3, 65, 1, 1), (4, 128, 17, 2), (7, 129, 200, 3), (8, 192, 40, 4), (9, 250, 90, 5), (6, 320, 150, 6),
+    (5, 383, 33, 7), (12, 448, 20, 8), (10, 512, 16, 9), (3, 512, 129, 10)])
+def test_step_sweep_matches_oracle(m, n, B, seed):
+    wl = workloads.random_crossbar(m, n, B, 7700 + seed, r_wl=1.5, r_bl=3.0, r_src=40.0, r_sense=60.0)
+    log(f"case {wl.name}")
+    ref = oracle.solve_workload(wl)
+    I, nv, (st, _) = gpu_solve(wl.G, wl.V, wl.geom, ordering="rows")
+    assert st == 0
+    assert rel_err(I, ref.currents).max() <= TOL_FP64 and node_rel_err(nv, ref.node_v).max() <= TOL_FP64
+    I2, _, _ = gpu_solve(wl.G, wl.V, wl.geom, node_voltages=False, ordering="rows")
+    assert np.array_equal(I, I2)
+
+
+@pytest.mark.parametrize("m,n", [(5, 512), (6, 300), (7, 128)])
+def test_step_sweep_same_bits_as_slab_sweep(m, n):
+    """The same vectors inside a batch past the step path's limit and in batches that take
+    each of its layouts."""
+    B = 16 * (4096 // (2 * ((n + 63) // 64 * 4))) + 16
+    wl = workloads.random_crossbar(m, n, B, 7800 + n)
+    log(f"case {wl.name}")
+    I, nv, (st, _) = gpu_solve(wl.G, wl.V, wl.geom, ordering="rows")
+    assert st == 0
+    for k in (1, 16, B // 16, B // 4 + 5, B // 2, B - 16):
+        Ik, nvk, _ = gpu_solve(wl.G, wl.V[:k], wl.geom, ordering="rows")
+        assert np.array_equal(Ik, I[:k]) and np.array_equal(nvk, nv[:k]), f"batch of {k}"
+
+
+def test_step_sweep_of_a_wide_crossbar():
+    """Inputs on the terminations (reciprocal ordering)."""
+    wl = workloads.random_crossbar(70, 90, 21, 7900, r_wl=1.5, r_bl=3.0, r_src=40.0, r_sense=60.0)
+    ref = oracle.solve_workload(wl)
+    I, nv, (st, _) = gpu_solve(wl.G, wl.V, wl.geom, ordering="smaller")
+    assert st == 0
+    assert rel_err(I, ref.currents).max() <= TOL_FP64 and node_rel_err(nv, ref.node_v).max() <= TOL_FP64
