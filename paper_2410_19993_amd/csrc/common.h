@@ -290,7 +290,8 @@ struct SweepArgs {
     // m-1, so the right-hand side is g_sense V[b][n-1-k] at row m-1 and zero elsewhere,
     // and the word lines have no sources
     int term = 0;
-    double* ysteps = nullptr;        // step path: [2 chains][2][nslab][16][n_p] right-hand side panels
+    void* ysteps = nullptr;          // step path: [2 chains][2][nslab][16][n_p] right-hand side panels
+    unsigned long long* norms = nullptr;   // refinement by steps: [nslab][16][2] bits of the largest |d|, |u|
 };
 
 struct ResidualArgs {
@@ -364,9 +365,10 @@ hipError_t xbk_launch_sweep(const xbk::SweepArgs& a, hipStream_t s);
 hipError_t xbk_launch_sweep_parts(const xbk::SweepArgs& a, hipStream_t s);   // one chain per workgroup, n_p > 64
 // float64 sweep of a plan (one crossbar): picks the kernels by block size and batch (sweep_rows.hip)
 hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s);
-int xbk_step_slabs(int n_p);        // slabs up to which it runs step by step over the GPU
+int xbk_step_slabs(int n_p, bool fp32);   // slabs up to which it runs step by step over the GPU
 hipError_t xbk_launch_recover(const xbk::RecoverArgs& a, hipStream_t s);
 hipError_t xbk_launch_sweep_ir(const xbk::SweepArgs& a, hipStream_t s);
+hipError_t xbk_launch_sweep_ir_plan(const xbk::SweepArgs& a, hipStream_t s);   // float32 counterpart of xbk_launch_sweep_plan
 hipError_t xbk_launch_residual(const xbk::ResidualArgs& a, hipStream_t s);
 int xbk_backward_error_max_n();     // widest crossbar the backward-error kernel measures
 // Krylov refinement kernels (gmres.hip); X_i = X + i P

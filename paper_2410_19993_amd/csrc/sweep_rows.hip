@@ -11,6 +11,10 @@
 //  * recover_rows_kernel: the word lines and node voltages of every row at once, from
 //    the solution the sweep left in the workspace.
 //
+// Panels of these kernels in memory (right-hand sides, forward results, solutions) are
+// 16 x n_p blocks in the fragment-tiled layout of H, so that a wave's access is contiguous;
+// the slab sweep's are [16][n_p] rows.
+//
 // The products, the order of their sums and the recovery are those of the slab sweep, so
 // an input vector's results have the same bits whichever kernel ran and whatever shares
 // its batch.
@@ -23,24 +27,42 @@ namespace xbk {
 namespace {
 
 typedef double d2v __attribute__((ext_vector_type(2)));
+template <typename T> struct R4;
+template <> struct R4<double> { using type = d4_t; };
+template <> struct R4<float> { using type = f4_t; };
 
 // A-operand fragment of an FRG tile.
-__device__ __forceinline__ d4_t frag_load(const double* __restrict__ tile, int l)
+template <typename T>
+__device__ __forceinline__ typename R4<T>::type frag_load(const T* __restrict__ tile, int l)
 {
-    const d2v lo = *reinterpret_cast<const d2v*>(tile + 2 * l);
-    const d2v hi = *reinterpret_cast<const d2v*>(tile + 128 + 2 * l);
-    return d4_t{lo[0], lo[1], hi[0], hi[1]};
+    if constexpr (sizeof(T) == 8) {
+        const d2v lo = *reinterpret_cast<const d2v*>(tile + 2 * l);
+        const d2v hi = *reinterpret_cast<const d2v*>(tile + 128 + 2 * l);
+        return d4_t{lo[0], lo[1], hi[0], hi[1]};
+    } else {
+        return *reinterpret_cast<const f4_t*>(tile + 4 * l);
+    }
 }
+__device__ __forceinline__ void frag_store(double* tile, int l, d4_t v)
+{
+    *reinterpret_cast<d2v*>(tile + 2 * l) = d2v{v[0], v[1]};
+    *reinterpret_cast<d2v*>(tile + 128 + 2 * l) = d2v{v[2], v[3]};
+}
+__device__ __forceinline__ void frag_store(float* tile, int l, f4_t v) { *reinterpret_cast<f4_t*>(tile + 4 * l) = v; }
 __device__ __forceinline__ d4_t load4(const double* p)
 {
     const d2v lo = *reinterpret_cast<const d2v*>(p), hi = *reinterpret_cast<const d2v*>(p + 2);
     return d4_t{lo[0], lo[1], hi[0], hi[1]};
 }
+__device__ __forceinline__ f4_t load4(const float* p) { return *reinterpret_cast<const f4_t*>(p); }
 __device__ __forceinline__ void store4(double* p, d4_t v)
 {
     *reinterpret_cast<d2v*>(p) = d2v{v[0], v[1]};
     *reinterpret_cast<d2v*>(p + 2) = d2v{v[2], v[3]};
 }
+__device__ __forceinline__ void store4(float* p, f4_t v) { *reinterpret_cast<f4_t*>(p) = v; }
+__device__ __forceinline__ double fma_t(double a, double b, double c) { return __builtin_fma(a, b, c); }
+__device__ __forceinline__ float fma_t(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 
 // ---------------------------------------------------------------------------
 // n <= 64 (n_p = 64), m >= 3.  Waves c LT + t: row tile t of chain c (0: rows from the
@@ -78,7 +100,7 @@ __global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
     const bool bval = b < a.B;
     const double g = a.g_bl;
     const double* const H = reinterpret_cast<const double*>(a.H) + (int64_t)t * (n_p >> 4) * 256;
-    double* const Z = reinterpret_cast<double*>(a.Z) + (int64_t)slab * m * 16 * n_p + col * n_p + 16 * t + 4 * q;
+    double* const Z = reinterpret_cast<double*>(a.Z) + (int64_t)slab * m * 16 * n_p + t * 256;
     const double* const C = a.c + 16 * t + q;                  // zero on the padding
     // input voltage of this lane's vector; reciprocal ordering: none (the terminations'
     // right-hand side of the last row is set apart)
@@ -109,7 +131,7 @@ __global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
         r = d4_t{ci[0], ci[4], ci[8], ci[12]};
     };
     auto rhs = [&](const d4_t& r, double v) { return r * (src ? v : 0.0); };
-    auto load_z = [&](int p, d4_t& r) { r = load4(Z + row_of(p) * zrow); };
+    auto load_z = [&](int p, d4_t& r) { r = frag_load<double>(Z + row_of(p) * zrow, l); };
     auto product = [&](const d4_t (&h)[LT], const double* y) {
         d4_t acc{0.0, 0.0, 0.0, 0.0};
 #pragma unroll
@@ -170,7 +192,7 @@ __global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
     auto forward = [&](int p, auto slot) {
         constexpr int d = decltype(slot)::value;
         const d4_t z = product(ring[d], pan[c][cur]);
-        store4(Z + row_of(p) * zrow, z);
+        frag_store(Z + row_of(p) * zrow, l, z);
         d4_t f = rhs(rq[(d + 1) % D], vq[(d + 1) % D]);
         if (p == 0 && idle) f = f0;
         // the next row's panel, or the forward result itself for the twist
@@ -201,7 +223,7 @@ __global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
     cur ^= 1;
     lds_barrier();
     const d4_t ut = product(ring[0], pan[c][cur]);
-    if (UP && c == 0) store4(Z + kt * zrow, ut);
+    if (UP && c == 0) frag_store(Z + kt * zrow, l, ut);
     store4(&pan[c][cur ^ 1][at], ut);
     load_h(F + D, ring[0]);
     load_z(F + D, rq[0]);
@@ -219,7 +241,7 @@ __global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
         u = axpy(product(ring[d], pan[c][cur]), rq[d]);
         if (UP) {
             if (idle && p == F + 1) u = ut;
-            store4(Z + row_of(p) * zrow, u);
+            frag_store(Z + row_of(p) * zrow, l, u);
         }
         store4(&pan[c][cur ^ 1][at], u);
         load_h(p + D, ring[d]);
@@ -266,11 +288,13 @@ __global__ __launch_bounds__(64 * kHelpers) void recover_rows_kernel(SweepArgs a
     double* coef = wv + 16 * PL;              // [3][PL] fr, ip, G of the row
     const double* U = reinterpret_cast<const double*>(a.Z) + ((int64_t)slab * m + i) * 16 * n_p;
     const int l = threadIdx.x & 63, h = threadIdx.x >> 6;
-    const int vecs = min(16, a.B - 16 * slab), used = (n + 15) & ~15;
-    // wave h copies the vectors it recovers
-    for (int v = h * R::VPW; v < min(vecs, (h + 1) * R::VPW); ++v)
-        for (int k = 2 * l; k < used; k += 128)
-            *reinterpret_cast<d2v*>(ybuf + v * ldy + k) = *reinterpret_cast<const d2v*>(U + (int64_t)v * n_p + k);
+    const int vecs = min(16, a.B - 16 * slab);
+    for (int e = threadIdx.x; e < 8 * ((n + 15) & ~15); e += 64 * kHelpers) {
+        const int le = e & 63, ce = le & 15;                 // 16 bytes of lane le of a tile
+        if (ce < vecs)
+            *reinterpret_cast<d2v*>(ybuf + ce * ldy + 16 * (e >> 7) + 4 * (le >> 4) + 2 * ((e >> 6) & 1)) =
+                *reinterpret_cast<const d2v*>(U + 2 * e);
+    }
     for (int j = threadIdx.x; j < n; j += 64 * kHelpers) {
         const int pj = padj(j, lg);
         const int64_t o = (int64_t)i * n + j;
@@ -303,50 +327,60 @@ hipError_t launch_recover_rows(const SweepArgs& a, hipStream_t s)
 // Bound: few vectors, the start of a launch and one wave's chain of n_p / 4 dependent
 // matrix instructions (K is not split: the sums keep the slab sweep's order); more, the
 // L2-to-L1 rate.  Measured a step (two rows) with one vector: 5.0 us at n_p = 256, 5.7 at
-// 320, 8.4 at 512, against 21, 35 and 70 us on one workgroup; 512 vectors at 512: 23.5
-// against 72 us.
+// 320, 8.0 at 512, against 21, 35 and 70 us on one workgroup; 512 vectors at 512: 17
+// against 72 us (24 with panels in rows, whose loads touch twice the cache lines).
 // Slabs up to which the steps are launches over the GPU (n_p > 128), and up to which each
 // chain has workgroups of its own.  Microseconds a step with node voltages, as launches /
-// chain per workgroup / slab per workgroup, 768 vectors: n = 512 33 / 37 / 72, n = 256
-// 12.1 / 11.6 / 22; 1024 vectors: 512 42 / 37 / 72, 320 23 / 18 / 36, 192 10.6 / 9.2 / 18;
-// 512 vectors: 23.5 / 37, 14 / 18.5, 7.4 / 9.2.  At n_p = 128 a step is too short to be a
-// launch (4.6 / 3.7 / 7.4 with one vector).
-constexpr int kStepSlabs = 48, kPartSlabs = 128;
+// chain per workgroup / slab per workgroup: 1024 vectors n = 512 28 / 37 / 72, 320 18.7 /
+// 18.4 / 36, 256 12.5 / 11.7 / 22, 192 9.1 / 9.3 / 18; 1536 vectors 40 / 38, 22 / 18.5,
+// 16.5 / 12.3.  At n_p = 128 a step is too short to be a launch (4.6 / 3.7 / 7.4 with one
+// vector).  Refinement sweeps (float32, with their residual) as launches / slab per
+// workgroup: 2048 vectors 38 / 48 at 512, 1536 vectors 21 / 27 at 320, 17 / 20 at 256.
+constexpr int kStepSlabs = 64, kPartSlabs = 128;
+constexpr int kStepSweeps = 6;      // refinement sweeps taken by steps
 
+template <typename T>
 struct StepJob {
     int row = -1;          // row whose product this is (-1: none)
     int next = -1;         // forward: row whose right-hand side panel follows (-1: none)
-    const double* pan = nullptr;   // panel of slab 0: [16][n_p], CPR
-    double* ynext = nullptr;       // forward: next panel of slab 0
+    const T* pan = nullptr;        // panel of slab 0 (16 x n_p, FRG)
+    T* ynext = nullptr;            // forward: next panel of slab 0
 };
+template <typename T>
 struct StepArgs {
     SweepArgs a;
-    StepJob job[2];
+    StepJob<T> job[2];
     int64_t pan_stride;    // elements between the panels of consecutive slabs
     int back;              // 0: forward or twist (u = H y), 1: u = z + g H u'
 };
 
-// Panels of the first rows (ra = rb = -1) or of the twist row, y = f + g z_ra + g z_rb.
-__global__ void step_form_kernel(SweepArgs a, int row0, double* y0, int row1, double* y1, int ra, int rb)
+// Panels of the first rows (ra = rb = -1) or of the twist row, y = f + g z_ra + g z_rb, with
+// f = V c, or in refinement sweeps past the first the residual.
+template <typename T>
+__global__ void step_form_kernel(SweepArgs a, int row0, T* y0, int row1, T* y1, int ra, int rb)
 {
     const int n_p = a.n_p, m = a.m, n = a.n;
     const int64_t panel = (int64_t)16 * n_p, total = panel * a.nslab;
     const int i = blockIdx.y == 0 ? row0 : row1;
-    double* y = blockIdx.y == 0 ? y0 : y1;
+    T* y = blockIdx.y == 0 ? y0 : y1;
     for (int64_t e = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; e < total; e += (int64_t)gridDim.x * blockDim.x) {
         const int64_t slab = e / panel, o = e - slab * panel;
-        const int p = (int)(o % n_p), b = (int)(16 * slab + o / n_p);
-        const int k = (p & ~15) + ((p & 15) >> 2) + 4 * (p & 3);             // CPR position -> k
+        int col, k;
+        frg_rc<T>(o, n_p, col, k);
+        const int b = (int)(16 * slab) + col;
         const bool bval = b < a.B;
-        double f = 0.0;
-        if (a.term) {
-            if (i == m - 1 && bval && k < n) f = a.g_sense * a.V[(int64_t)b * n + (n - 1 - k)];
+        T f = 0;
+        if (sizeof(T) == 4 && a.iter > 0) {
+            if (k < n) f = reinterpret_cast<const T*>(a.R)[slab * m * panel + i * panel + cpr<T>(col, k, n_p)];
+        } else if (a.term) {
+            if (i == m - 1 && bval && k < n) f = (T)(a.g_sense * a.V[(int64_t)b * n + (n - 1 - k)]);
         } else if (bval) {
-            f = a.c[(int64_t)i * n_p + k] * a.V[(int64_t)b * m + i];
+            f = (T)(a.c[(int64_t)i * n_p + k] * a.V[(int64_t)b * m + i]);
         }
-        const double* Zs = reinterpret_cast<const double*>(a.Z) + slab * m * panel + o;
-        if (ra >= 0) f = __builtin_fma(a.g_bl, Zs[ra * panel], f);
-        if (rb >= 0) f = __builtin_fma(a.g_bl, Zs[rb * panel], f);
+        const T* Zs = reinterpret_cast<const T*>(a.Z) + slab * m * panel + o;
+        const T g = (T)a.g_bl;
+        if (ra >= 0) f = fma_t(g, Zs[ra * panel], f);
+        if (rb >= 0) f = fma_t(g, Zs[rb * panel], f);
         y[e] = f;
     }
 }
@@ -354,9 +388,16 @@ __global__ void step_form_kernel(SweepArgs a, int row0, double* y0, int row1, do
 // One wave a workgroup: row tile idx % KC, S slabs.  Workgroup b runs on XCD b % 8: with
 // two jobs each chain has four XCDs, and consecutive workgroups of an XCD group take
 // consecutive row tiles, so an XCD's L2 holds a quarter of each H block.
-template <int NT, int S>
-__global__ __launch_bounds__(64) void sweep_step_kernel(StepArgs sa)
+//
+// float: the sweeps of the refinement.  A solution row is then the correction d; it is
+// added to the float64 solution at once, and the largest |d| and |u| of each vector go
+// to a.norms as bit patterns (their order is that of the non-negative numbers, a NaN
+// above all), for step_decide_kernel.
+template <typename T, int NT, int S>
+__global__ __launch_bounds__(64) void sweep_step_kernel(StepArgs<T> sa)
 {
+    using v4 = typename R4<T>::type;
+    constexpr bool IR = sizeof(T) == 4;
     constexpr int n_p = 64 * NT, KC = 4 * NT;
     constexpr int PF = S == 1 ? 12 : 6;                    // chunks in flight
     const SweepArgs& a = sa.a;
@@ -366,111 +407,189 @@ __global__ __launch_bounds__(64) void sweep_step_kernel(StepArgs sa)
     const int idx = two ? local * 4 + (xcd & 3) : blockIdx.x;
     const int t = idx % KC, slab0 = (idx / KC) * S;
     if (slab0 >= a.nslab) return;
+    const int last = a.nslab - 1;                          // slabs past the last repeat it, unstored
+    bool live[S];
+    bool any = false;
+#pragma unroll
+    for (int s = 0; s < S; ++s) {
+        live[s] = slab0 + s <= last && !(IR && a.iter > 0 && a.slab_done[min(slab0 + s, last)]);
+        any |= live[s];
+    }
+    if (!any) return;
     const int row = c == 0 ? sa.job[0].row : sa.job[1].row;
     const int next = c == 0 ? sa.job[0].next : sa.job[1].next;
-    const double* const pan = c == 0 ? sa.job[0].pan : sa.job[1].pan;
-    double* const ynext = c == 0 ? sa.job[0].ynext : sa.job[1].ynext;
+    const T* const pan = c == 0 ? sa.job[0].pan : sa.job[1].pan;
+    T* const ynext = c == 0 ? sa.job[0].ynext : sa.job[1].ynext;
     const int l = threadIdx.x & 63, q = l >> 4, col = l & 15;
     const int m = a.m, n = a.n;
-    const double* const H = reinterpret_cast<const double*>(a.H) + (int64_t)row * n_p * n_p + (int64_t)t * KC * 256;
-    const int last = a.nslab - 1;                          // slabs past the last repeat it, unstored
-    const double* y[S];
+    const T* const H = reinterpret_cast<const T*>(a.H) + (int64_t)row * n_p * n_p + (int64_t)t * KC * 256;
+    const T* y[S];
 #pragma unroll
     for (int s = 0; s < S; ++s)
-        y[s] = pan + min(slab0 + s, last) * sa.pan_stride + col * n_p + 4 * q;
-    d4_t hr[PF], yr[PF][S], acc[S];
+        y[s] = pan + min(slab0 + s, last) * sa.pan_stride;
+    v4 hr[PF], yr[PF][S], acc[S];
 #pragma unroll
     for (int k = 0; k < PF; ++k) {
         hr[k] = frag_load(H + k * 256, l);
 #pragma unroll
-        for (int s = 0; s < S; ++s) yr[k][s] = load4(y[s] + 16 * k);
+        for (int s = 0; s < S; ++s) yr[k][s] = frag_load(y[s] + 256 * k, l);
     }
-    // requested before the product, used after it
-    const int o = col * n_p + 16 * t + 4 * q;
-    double* const Z = reinterpret_cast<double*>(a.Z) + (int64_t)row * 16 * n_p + o;
-    const int64_t zslab = (int64_t)m * 16 * n_p;
-    const bool fwd = next >= 0;
-    d4_t e[S], cn{0.0, 0.0, 0.0, 0.0};
+    // requested before the product, used after it: the forward result (back), or the next
+    // row's right-hand side
+    const int o = col * n_p + 16 * t + 4 * q;              // in the refinement's CPR panels
+    const int64_t rowo = (int64_t)row * 16 * n_p + o, zslab = (int64_t)m * 16 * n_p;
+    T* const Z = reinterpret_cast<T*>(a.Z) + (int64_t)row * 16 * n_p + 256 * t;
+    const bool fwd = next >= 0, resid = IR && a.iter > 0;
+    v4 e[S];
+    d4_t cn{0.0, 0.0, 0.0, 0.0}, up[IR ? S : 1];
+    double vn[S];
     if (sa.back) {
 #pragma unroll
-        for (int s = 0; s < S; ++s) e[s] = load4(Z + min(slab0 + s, last) * zslab);
+        for (int s = 0; s < S; ++s) e[s] = frag_load<T>(Z + min(slab0 + s, last) * zslab, l);
+    } else if (resid) {
+        const T* R = reinterpret_cast<const T*>(a.R) + (int64_t)(fwd ? next : 0) * 16 * n_p + o;
+#pragma unroll
+        for (int s = 0; s < S; ++s) e[s] = load4(R + min(slab0 + s, last) * zslab);
     } else {
-        const double* ci = a.c + (int64_t)(fwd ? next : 0) * n_p + 16 * t + q;
-        cn = d4_t{ci[0], ci[4], ci[8], ci[12]};
+        const double* ci = a.c + (int64_t)(fwd ? next : 0) * n_p + 16 * t;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) cn[v] = ci[Frag<T>::drow(q, v)];
 #pragma unroll
         for (int s = 0; s < S; ++s) {
             const int b = 16 * (slab0 + s) + col;
             const bool src = fwd && b < a.B && !a.term;
             const double v = a.V[src ? (int64_t)b * m + next : 0];
-            e[s] = d4_t{src ? v : 0.0, 0.0, 0.0, 0.0};
+            vn[s] = src ? v : 0.0;
         }
     }
+    if (IR && !fwd) {
+        // a solution row (forward rows without a next one are loaded in vain)
 #pragma unroll
-    for (int s = 0; s < S; ++s) acc[s] = d4_t{0.0, 0.0, 0.0, 0.0};
+        for (int s = 0; s < S; ++s)
+            up[IR ? s : 0] = a.iter > 0 ? load4(a.Uin + rowo + min(slab0 + s, last) * zslab) : d4_t{0.0, 0.0, 0.0, 0.0};
+    }
+#pragma unroll
+    for (int s = 0; s < S; ++s) acc[s] = v4{0, 0, 0, 0};
 #pragma unroll
     for (int k = 0; k < KC; ++k) {
 #pragma unroll
         for (int j = 0; j < 4; ++j)
 #pragma unroll
-            for (int s = 0; s < S; ++s) acc[s] = Frag<double>::mma(hr[k % PF][j], yr[k % PF][s][j], acc[s]);
+            for (int s = 0; s < S; ++s) acc[s] = Frag<T>::mma(hr[k % PF][j], yr[k % PF][s][j], acc[s]);
         if (k + PF < KC) {
             hr[k % PF] = frag_load(H + (k + PF) * 256, l);
 #pragma unroll
-            for (int s = 0; s < S; ++s) yr[k % PF][s] = load4(y[s] + 16 * (k + PF));
+            for (int s = 0; s < S; ++s) yr[k % PF][s] = frag_load(y[s] + 256 * (k + PF), l);
         }
     }
+    const T g = (T)a.g_bl;
+    const bool solution = sa.back || row == m / 2;
 #pragma unroll
     for (int s = 0; s < S; ++s) {
-        const int slab = slab0 + s;
-        if (slab > last) break;
-        d4_t u = acc[s];
+        if (!live[s]) continue;
+        const int slab = slab0 + s, b = 16 * slab + col;
+        v4 u = acc[s];
         if (sa.back) {
 #pragma unroll
-            for (int v = 0; v < 4; ++v) u[v] = __builtin_fma(a.g_bl, u[v], e[s][v]);
+            for (int v = 0; v < 4; ++v) u[v] = fma_t(g, u[v], e[s][v]);
         }
-        store4(Z + slab * zslab, u);
+        frag_store(Z + slab * zslab, l, u);
         if (fwd) {
-            const d4_t f = cn * e[s][0];
-            d4_t yn;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) yn[v] = __builtin_fma(a.g_bl, u[v], f[v]);
-            store4(ynext + (int64_t)slab * 16 * n_p + o, yn);
-        }
-        // the last row's solution: a back step's, or the twist's when it is the last row
-        if (row == m - 1 && (sa.back || m - 1 == m / 2)) {
-            const int b = 16 * slab + col;
+            v4 yn;
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
-                const int k = 16 * t + Frag<double>::drow(q, v);
-                if (b < a.B && k < n) a.Iout[(int64_t)b * n + k] = a.g_sense * u[v];
+                const T f = resid ? (16 * t + Frag<T>::drow(q, v) < n ? e[s][v] : (T)0) : (T)(cn[v] * vn[s]);
+                yn[v] = fma_t(g, u[v], f);
+            }
+            frag_store(ynext + (int64_t)slab * 16 * n_p + 256 * t, l, yn);
+        }
+        if (!solution) continue;
+        d4_t x;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = (double)u[v];
+        if constexpr (IR) {
+            double dm = 0.0, um = 0.0;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const double d = x[v];
+                x[v] = up[s][v] + d;
+                dm = nan_max(dm, fabs(d));
+                um = nan_max(um, fabs(x[v]));
+            }
+            store4(a.Uout + rowo + slab * zslab, x);
+            if (a.tol >= 0.0) {
+                for (int off = 16; off < 64; off <<= 1) {
+                    dm = nan_max(dm, __shfl_xor(dm, off));
+                    um = nan_max(um, __shfl_xor(um, off));
+                }
+                if (q == 0) {
+                    unsigned long long* key = a.norms + 2 * (int64_t)b;
+                    atomicMax(key, __builtin_bit_cast(unsigned long long, fabs(dm)));
+                    atomicMax(key + 1, __builtin_bit_cast(unsigned long long, fabs(um)));
+                }
+            }
+        }
+        if (row == m - 1) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = 16 * t + Frag<T>::drow(q, v);
+                if (b < a.B && k < n) a.Iout[(int64_t)b * n + k] = a.g_sense * x[v];
             }
         }
     }
 }
 
-template <int NT, int S>
-hipError_t launch_step(const StepArgs& sa, hipStream_t s)
+// Refinement bookkeeping of every slab after a sweep by steps (the slab sweep's own rule:
+// SweepCtx::decide); clears the norms for the next sweep.
+__global__ __launch_bounds__(64) void step_decide_kernel(SweepArgs a)
+{
+    const int slab = blockIdx.x * 4 + (threadIdx.x >> 4), c = threadIdx.x & 15;
+    const bool open = slab < a.nslab && !(a.iter > 0 && a.slab_done[slab]);
+    bool ok = true;
+    if (open) {
+        unsigned long long* key = a.norms + 2 * (16 * (int64_t)slab + c);
+        const double D = __builtin_bit_cast(double, key[0]), U = __builtin_bit_cast(double, key[1]);
+        key[0] = key[1] = 0ull;
+        double* dprev = a.dnorm + (int64_t)slab * 16 + c;
+        const double est = (a.iter > 0 && *dprev > 0.0) ? D * fmin(1.0, D / *dprev) : D;
+        ok = (D == 0.0) || (a.iter > 0 && est <= a.tol * U);
+        *dprev = D;
+    }
+    const unsigned long long bad = __ballot(!ok) >> (threadIdx.x & 48) & 0xffffull;
+    if (open && c == 0) {
+        const bool all = bad == 0, last = a.iter + 1 >= a.max_iter;
+        if (all || last) {
+            a.slab_done[slab] = 1;
+            a.slab_final[slab] = (a.iter + 1) & 1;
+            atomicMax(a.flags + kIrIters, a.iter + 1);
+            if (!all) atomicOr(a.flags + kErrConv, 1);
+        }
+    }
+}
+
+template <typename T, int NT, int S>
+hipError_t launch_step(const StepArgs<T>& sa, hipStream_t s)
 {
     const int work = 4 * NT * ((sa.a.nslab + S - 1) / S);
     const bool two = sa.job[0].row >= 0 && sa.job[1].row >= 0;
-    hipLaunchKernelGGL((sweep_step_kernel<NT, S>), dim3(two ? 8 * ((work + 3) / 4) : work), dim3(64), 0, s, sa);
+    hipLaunchKernelGGL((sweep_step_kernel<T, NT, S>), dim3(two ? 8 * ((work + 3) / 4) : work), dim3(64), 0, s, sa);
     return hipGetLastError();
 }
 
-template <int NT, int S>
+template <typename T, int NT, int S>
 hipError_t run_steps(const SweepArgs& a, hipStream_t s)
 {
     const int m = a.m, kt = m / 2;
     const int64_t row = (int64_t)16 * a.n_p, panel = row * a.nslab;
-    double* const Y = a.ysteps;                            // [2 chains][2][nslab][16][n_p]
-    double* const Z = reinterpret_cast<double*>(a.Z);
+    T* const Y = reinterpret_cast<T*>(a.ysteps);           // [2 chains][2][nslab][16][n_p]
+    T* const Z = reinterpret_cast<T*>(a.Z);
     const unsigned blocks = (unsigned)std::min<int64_t>((panel + 255) / 256, 2048);
-    const bool bottom = kt + 1 < m;
-    StepArgs sa;
+    const bool bottom = kt + 1 < m, up = a.node_v != nullptr || sizeof(T) == 4;
+    StepArgs<T> sa;
     sa.a = a;
     hipError_t e = hipSuccess;
     if (kt > 0) {
-        hipLaunchKernelGGL(step_form_kernel, dim3(blocks, bottom ? 2 : 1), dim3(256), 0, s, a, 0, Y, m - 1,
+        hipLaunchKernelGGL(step_form_kernel<T>, dim3(blocks, bottom ? 2 : 1), dim3(256), 0, s, a, 0, Y, m - 1,
                            Y + 2 * panel, -1, -1);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
@@ -480,23 +599,23 @@ hipError_t run_steps(const SweepArgs& a, hipStream_t s)
         const int rows[2] = {p, m - 1 - p > kt ? m - 1 - p : -1};
         const int next[2] = {p + 1 < kt ? p + 1 : -1, m - 2 - p > kt ? m - 2 - p : -1};
         for (int c = 0; c < 2; ++c)
-            sa.job[c] = StepJob{rows[c], next[c], Y + (2 * c + (p & 1)) * panel, Y + (2 * c + ((p + 1) & 1)) * panel};
-        if ((e = launch_step<NT, S>(sa, s)) != hipSuccess) return e;
+            sa.job[c] = StepJob<T>{rows[c], next[c], Y + (2 * c + (p & 1)) * panel, Y + (2 * c + ((p + 1) & 1)) * panel};
+        if ((e = launch_step<T, NT, S>(sa, s)) != hipSuccess) return e;
     }
-    hipLaunchKernelGGL(step_form_kernel, dim3(blocks), dim3(256), 0, s, a, kt, Y, 0, nullptr, kt > 0 ? kt - 1 : -1,
-                       bottom ? kt + 1 : -1);
+    hipLaunchKernelGGL(step_form_kernel<T>, dim3(blocks), dim3(256), 0, s, a, kt, Y, 0, (T*)nullptr,
+                       kt > 0 ? kt - 1 : -1, bottom ? kt + 1 : -1);
     if ((e = hipGetLastError()) != hipSuccess) return e;
-    sa.job[0] = StepJob{kt, -1, Y, nullptr};
-    sa.job[1] = StepJob{};
-    if ((e = launch_step<NT, S>(sa, s)) != hipSuccess) return e;
+    sa.job[0] = StepJob<T>{kt, -1, Y, nullptr};
+    sa.job[1] = StepJob<T>{};
+    if ((e = launch_step<T, NT, S>(sa, s)) != hipSuccess) return e;
     sa.pan_stride = m * row;
     sa.back = 1;
     for (int p = 1; p <= kt; ++p) {
         // without node voltages only the rows below the twist (the currents' row is the last)
-        sa.job[0] = a.node_v ? StepJob{kt - p, -1, Z + (kt - p + 1) * row, nullptr} : StepJob{};
-        sa.job[1] = kt + p < m ? StepJob{kt + p, -1, Z + (kt + p - 1) * row, nullptr} : StepJob{};
+        sa.job[0] = up ? StepJob<T>{kt - p, -1, Z + (kt - p + 1) * row, nullptr} : StepJob<T>{};
+        sa.job[1] = kt + p < m ? StepJob<T>{kt + p, -1, Z + (kt + p - 1) * row, nullptr} : StepJob<T>{};
         if (sa.job[0].row < 0 && sa.job[1].row < 0) break;
-        if ((e = launch_step<NT, S>(sa, s)) != hipSuccess) return e;
+        if ((e = launch_step<T, NT, S>(sa, s)) != hipSuccess) return e;
     }
     return hipSuccess;
 }
@@ -511,26 +630,38 @@ hipError_t launch_small(const SweepArgs& a, hipStream_t s)
     return hipGetLastError();
 }
 
-// One slab a wave up to a wave per SIMD, two (on each H tile it loads) past that: at
-// 512 x 512, 512 vectors, 23.5 against 24.7 us a step, at 16 vectors 10.7 against 8.4.
-// (Four row tiles a workgroup, so that they share the panels in its L1, and four slabs a
-// wave were slower at every size: 9.1 to 34 us at 16 vectors.)
+// One slab a wave up to a wave per SIMD, two (on each H tile it loads) past that: with
+// 1024 vectors at n = 512 27.8 against 32.4 us a step, with 16 vectors 10.7 against 8.0.
+// (Four slabs a wave, or four row tiles a workgroup to share panels in its L1, were
+// slower or equal everywhere.)
 template <int NT>
 hipError_t run_steps_nt(const SweepArgs& a, hipStream_t s)
 {
     const int waves = 2 * (4 * NT) * a.nslab;
-    const hipError_t e = waves <= 1024 ? run_steps<NT, 1>(a, s) : run_steps<NT, 2>(a, s);
+    const hipError_t e = waves <= 1024 ? run_steps<double, NT, 1>(a, s) : run_steps<double, NT, 2>(a, s);
     if (e != hipSuccess || !a.node_v) return e;
     return launch_recover_rows<NT>(a, s);
+}
+
+// (float32 products are half as long: one slab a wave up to four waves per SIMD, 18.3
+// against 21.0 us a step with 512 vectors at n = 512, 26.6 against 25.9 with 1024)
+template <int NT>
+hipError_t run_ir_steps_nt(const SweepArgs& a, hipStream_t s)
+{
+    const int waves = 2 * (4 * NT) * a.nslab;
+    const hipError_t e = waves < 4096 ? run_steps<float, NT, 1>(a, s) : run_steps<float, NT, 2>(a, s);
+    if (e != hipSuccess || a.tol < 0.0) return e;
+    hipLaunchKernelGGL(step_decide_kernel, dim3((a.nslab + 3) / 4), dim3(64), 0, s, a);
+    return hipGetLastError();
 }
 
 }  // namespace
 
 }  // namespace xbk
 
-int xbk_step_slabs(int n_p)
+int xbk_step_slabs(int n_p, bool fp32)
 {
-    return n_p > 128 ? xbk::kStepSlabs : 0;
+    return n_p <= 128 ? 0 : fp32 ? xbk::kPartSlabs : xbk::kStepSlabs;
 }
 
 hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s)
@@ -550,7 +681,7 @@ hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s)
         return xbk::launch_recover_rows<1>(a, s);
     }
     if (a.nslab > xbk::kPartSlabs) return xbk_launch_sweep(a, s);
-    if (a.ysteps == nullptr || a.nslab > xbk_step_slabs(a.n_p)) return xbk_launch_sweep_parts(a, s);
+    if (a.ysteps == nullptr || a.nslab > xbk_step_slabs(a.n_p, false)) return xbk_launch_sweep_parts(a, s);
     switch (a.n_p / 64) {
         case 3: return xbk::run_steps_nt<3>(a, s);
         case 4: return xbk::run_steps_nt<4>(a, s);
@@ -558,6 +689,22 @@ hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s)
         case 6: return xbk::run_steps_nt<6>(a, s);
         case 7: return xbk::run_steps_nt<7>(a, s);
         case 8: return xbk::run_steps_nt<8>(a, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t xbk_launch_sweep_ir_plan(const xbk::SweepArgs& a, hipStream_t s)
+{
+    // past the sweeps that a slab needs, the slab sweep, whose launch ends at once
+    if (a.m < 3 || a.ysteps == nullptr || a.nslab > xbk_step_slabs(a.n_p, true) || a.iter >= xbk::kStepSweeps)
+        return xbk_launch_sweep_ir(a, s);
+    switch (a.n_p / 64) {
+        case 3: return xbk::run_ir_steps_nt<3>(a, s);
+        case 4: return xbk::run_ir_steps_nt<4>(a, s);
+        case 5: return xbk::run_ir_steps_nt<5>(a, s);
+        case 6: return xbk::run_ir_steps_nt<6>(a, s);
+        case 7: return xbk::run_ir_steps_nt<7>(a, s);
+        case 8: return xbk::run_ir_steps_nt<8>(a, s);
         default: return hipErrorInvalidValue;
     }
 }

@@ -30,7 +30,7 @@ struct Buffers {
     double* Iout = nullptr;   // [max_batch][n]
     int* flags = nullptr;     // [kNumFlags]
     unsigned long long* diag = nullptr;   // [kNumDiag]: smallest pivot key, largest backward error bits
-    double* ysteps = nullptr; // [2 chains][2][slabs][16][n_p]: panels of the step path
+    void* ysteps = nullptr;   // [2 chains][2][slabs][16][n_p]: panels of the step path
     double* sink = nullptr;   // [128]: target of the sweep's L2-pull keep-alive store
     // Newton-Schulz factor: per chain S, X[2], Q ([n_p][n_p]) and dprev ([2][n_p])
     void* ns_S[2] = {nullptr, nullptr};
@@ -43,6 +43,7 @@ struct Buffers {
     double* U[2] = {nullptr, nullptr};       // [nslab][m][16][n_p]
     void* R = nullptr;                       // [nslab][m][16][n_p] float
     double* dnorm = nullptr;                 // [nslab][16]
+    unsigned long long* norms = nullptr;     // [nslab][16][2] largest |d|, |u| of a sweep by steps
     int* slab_done = nullptr;                // [nslab]
     int* slab_final = nullptr;               // [nslab]
     double* Vunit = nullptr;                 // [tr_rows][m]: unit inputs of xbar_transfer (plans
@@ -65,11 +66,14 @@ struct Buffers {
     double* nv_rev = nullptr;
 };
 
-__global__ void clear_slabs_kernel(int* done, double* dnorm, int nslab)
+__global__ void clear_slabs_kernel(int* done, double* dnorm, unsigned long long* norms, int nslab)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < nslab) done[i] = 0;
-    if (i < 16 * nslab) dnorm[i] = 0.0;
+    if (i < 16 * nslab) {
+        dnorm[i] = 0.0;
+        norms[2 * i] = norms[2 * i + 1] = 0ull;
+    }
 }
 
 __global__ void clear_flags_kernel(int* f)
@@ -183,7 +187,7 @@ void free_all(xbar_plan p)
                    d.ns_S[0], d.ns_S[1], d.ns_X[0][0], d.ns_X[0][1], d.ns_X[1][0], d.ns_X[1][1],
                    d.ns_Q[0], d.ns_Q[1],
                    d.ns_dprev[0], d.ns_dprev[1], d.ns_part, d.ns_state,
-                   d.U[0], d.U[1], d.R, d.dnorm, d.slab_done, d.slab_final, d.Vunit,
+                   d.U[0], d.U[1], d.R, d.dnorm, d.norms, d.slab_done, d.slab_final, d.Vunit,
                    d.gm_V, d.gm_Z, d.gm_zero, d.gm_part, d.gm_H, d.gm_beta, d.gm_y, d.gm_coef,
                    d.Grev, d.nv_rev};
     for (void* x : all)
@@ -394,8 +398,8 @@ xbar_status xbar_create_ordered(const xbar_geometry* geom, xbar_precision prec, 
     }
     A((void**)&d.ns_part, 2 * (n_p / 32) * (n_p / 32) * 8);
     A((void**)&d.ns_state, 6 * sizeof(xbk::NSState));
-    if (prec == XBAR_FP64 && xbk_step_slabs(p->n_p) > 0)
-        A((void**)&d.ysteps, 4 * (int64_t)std::min(p->nslab_max, xbk_step_slabs(p->n_p)) * 16 * n_p * 8);
+    if (xbk_step_slabs(p->n_p, p->fp32()) > 0)
+        A(&d.ysteps, 4 * (int64_t)std::min(p->nslab_max, xbk_step_slabs(p->n_p, p->fp32())) * 16 * n_p * es);
     if (!transfer_blocks_fit(p)) A((void**)&d.Vunit, (int64_t)p->tr_rows * og.m * 8);
     if (rev) {
         A((void**)&d.Grev, m * n * 8);
@@ -407,6 +411,7 @@ xbar_status xbar_create_ordered(const xbar_geometry* geom, xbar_precision prec, 
         A((void**)&d.U[1], panel * 8);
         A(&d.R, panel * 4);
         A((void**)&d.dnorm, (int64_t)p->nslab_max * 16 * 8);
+        A((void**)&d.norms, (int64_t)p->nslab_max * 16 * 2 * 8);
         A((void**)&d.slab_done, (int64_t)p->nslab_max * 4);
         A((void**)&d.slab_final, (int64_t)p->nslab_max * 4);
         if (prec == XBAR_BF16_GMRES_IR) {
@@ -875,7 +880,7 @@ xbar_status gmres_solve(xbar_plan p, xbk::SweepArgs s, xbk::ResidualArgs r, int 
         s.Uin = uin;
         s.Uout = uout;
         if (p->timing && !p->t_ir_sweep.begin(p->stream)) return false;
-        if (!ok(xbk_launch_sweep_ir(s, p->stream))) return false;
+        if (!ok(xbk_launch_sweep_ir_plan(s, p->stream))) return false;
         return !p->timing || p->t_ir_sweep.end(p->stream);
     };
     auto resid = [&](const double* u, double* out, int matvec) {
@@ -964,11 +969,12 @@ xbar_status xbar_solve_batch(xbar_plan p, const double* V, int32_t B, double* no
         // float sweeps refined in float64: sweep 0 solves with V c, each later sweep
         // corrects U by the solution for the float64 residual of the previous U.
         hipLaunchKernelGGL(clear_slabs_kernel, dim3((16 * nslab + 255) / 256), dim3(256), 0, p->stream,
-                           p->d.slab_done, p->d.dnorm, nslab);
+                           p->d.slab_done, p->d.dnorm, p->d.norms, nslab);
         s.max_iter = 1 + p->ir_max_iter;
         s.tol = p->ir_tol;
         s.R = p->d.R;
         s.dnorm = p->d.dnorm;
+        s.norms = p->d.norms;
         s.slab_done = p->d.slab_done;
         s.slab_final = p->d.slab_final;
         xbk::ResidualArgs r{};
@@ -1005,7 +1011,7 @@ xbar_status xbar_solve_batch(xbar_plan p, const double* V, int32_t B, double* no
                 if (p->timing && !p->t_residual.end(p->stream)) return XBAR_ERR_DEVICE;
             }
             if (p->timing && !p->t_ir_sweep.begin(p->stream)) return XBAR_ERR_DEVICE;
-            if (xbk_launch_sweep_ir(s, p->stream) != hipSuccess) return XBAR_ERR_DEVICE;
+            if (xbk_launch_sweep_ir_plan(s, p->stream) != hipSuccess) return XBAR_ERR_DEVICE;
             if (p->timing && !p->t_ir_sweep.end(p->stream)) return XBAR_ERR_DEVICE;
         }
     }

@@ -11,7 +11,7 @@ import pytest
 
 import oracle
 import workloads
-from tests.gpu_util import TOL_FP64, gpu_solve, log, node_rel_err, rel_err
+from tests.gpu_util import TOL_FP64, TOL_IR, gpu_solve, log, node_rel_err, rel_err
 
 pytestmark = pytest.mark.gpu
 
@@ -34,12 +34,12 @@ def test_step_sweep_matches_oracle(m, n, B, seed):
 def test_step_sweep_same_bits_as_slab_sweep(m, n):
     """The same vectors inside a batch past the step path's limit and in batches that take
     each of its layouts."""
-    B = 16 * (4096 // (2 * ((n + 63) // 64 * 4))) + 16
+    B = 16 * 129                       # past the step path and the chain per workgroup
     wl = workloads.random_crossbar(m, n, B, 7800 + n)
     log(f"case {wl.name}")
     I, nv, (st, _) = gpu_solve(wl.G, wl.V, wl.geom, ordering="rows")
     assert st == 0
-    for k in (1, 16, B // 16, B // 4 + 5, B // 2, B - 16):
+    for k in (1, 17, 16 * 20 + 3, 16 * 64, 16 * 65, B - 16):
         Ik, nvk, _ = gpu_solve(wl.G, wl.V[:k], wl.geom, ordering="rows")
         assert np.array_equal(Ik, I[:k]) and np.array_equal(nvk, nv[:k]), f"batch of {k}"
 
@@ -51,3 +51,20 @@ def test_step_sweep_of_a_wide_crossbar():
     I, nv, (st, _) = gpu_solve(wl.G, wl.V, wl.geom, ordering="smaller")
     assert st == 0
     assert rel_err(I, ref.currents).max() <= TOL_FP64 and node_rel_err(nv, ref.node_v).max() <= TOL_FP64
+
+
+@pytest.mark.parametrize("m,n,B,seed", [(3, 129, 1, 1), (6, 250, 130, 2), (7, 320, 48, 3), (9, 512, 300, 4)])
+def test_refinement_by_steps(m, n, B, seed):
+    """The refinement's float32 sweeps by steps: within the refinement's tolerance (1e-9),
+    and the bits and sweep count of the slab sweep, which a larger batch takes."""
+    wl = workloads.random_crossbar(m, n, B, 7950 + seed, r_wl=1.5, r_bl=3.0, r_src=40.0, r_sense=60.0)
+    log(f"case {wl.name} fp32_ir")
+    ref = oracle.solve_workload(wl)
+    I, nv, (st, info) = gpu_solve(wl.G, wl.V, wl.geom, "fp32_ir", ordering="rows")
+    assert st == 0
+    assert rel_err(I, ref.currents).max() <= TOL_IR and node_rel_err(nv, ref.node_v).max() <= TOL_IR
+    V = np.tile(wl.V, (-(-(16 * 128 + 1) // B), 1))
+    Ib, nvb, (stb, infob) = gpu_solve(wl.G, V, wl.geom, "fp32_ir", ordering="rows")
+    assert stb == 0 and infob.ir_iters == info.ir_iters
+    k = B // 16 * 16                   # a slab stops as a whole: compare whole ones
+    assert np.array_equal(Ib[:k], I[:k]) and np.array_equal(nvb[:k], nv[:k])
