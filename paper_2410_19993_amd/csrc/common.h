@@ -313,6 +313,7 @@ struct ResidualArgs {
     int matvec = 0;
     int term = 0;        // reciprocal ordering (see SweepArgs::term); V is [B][n]
     double g_sense = 0.0;
+    int chunk = 0;       // rows per workgroup (set by the launcher)
 };
 
 // Krylov refinement (gmres.hip): restart length and the panel geometry its batched
@@ -338,6 +339,7 @@ struct RecoverArgs {
     double g_wl;
     double* node_v;      // [B][2mn]
     int term = 0;        // reciprocal ordering: no word-line sources
+    int chunk = 0;       // rows per workgroup (set by the launcher)
 };
 
 // Normwise backward error of node voltages (diagnostics.hip).

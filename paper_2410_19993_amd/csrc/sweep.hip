@@ -20,6 +20,8 @@
 // load instruction of a wave reads 1 KB of contiguous memory).  W waves (8 when n_p/64 is
 // even, else 4) each own a band of TW = 4 n_p / (64 W) tiles of 16 rows, so
 // that the accumulators and one chunk of prefetched H stay in registers.
+#include <algorithm>
+
 #include "recover.h"
 #include "xbar.h"
 
@@ -854,9 +856,11 @@ __device__ __forceinline__ void tridiag_solve_masked(double* __restrict__ d, con
 }
 
 // Row walkers of the refinement: one workgroup per half slab (8 input vectors,
-// 32 lanes each) walks the rows i = 0..m-1, so that every row of the float64
-// solution is read from memory once (a lane keeps elements j = s + 32k of the
-// rows it still needs in registers).  The next row of the solution and of the
+// 32 lanes each) and chunk of rows (blockIdx.y) walks its rows, so that every row of the
+// float64 solution is read from memory once (a lane keeps elements j = s + 32k of the
+// rows it still needs in registers).  Few slabs take more chunks: a row is about 6 us of
+// dependent solves, and 512 vectors in one chunk kept 64 of the 256 CUs busy (residual
+// 2.9 ms, recovery 3.75 ms at 512 x 512; 0.45 and 0.67 ms with 8 chunks).  The next row of the solution and of the
 // coefficients is requested before a row's tridiagonal solve, so that its
 // latency hides behind it; the coefficients pass through double-buffered LDS.  One workgroup barrier per
 // row publishes the next row's coefficients.
@@ -923,24 +927,24 @@ __device__ __forceinline__ void residual_walk(const ResidualArgs& a, unsigned ch
     const double* const src[5] = {a.fr, a.ip, a.Gc, a.c, a.q};
     const int ld[5] = {n, n, n, n_p, n};
     RowCoeffs<5> rc;
+    const int i0 = (int)blockIdx.y * a.chunk, i1 = min(m, i0 + a.chunk);
     double up[kRwJ], uc[kRwJ];
 #pragma unroll
     for (int k = 0; k < kRwJ; ++k) up[k] = 0.0;
-    rw_load_row(U, n, s, uc);
-    rc.load(src, ld, 0, n);
+    if (i0 > 0) rw_load_row(U + (i0 - 1) * rs, n, s, up);
+    rw_load_row(U + i0 * rs, n, s, uc);
+    rc.load(src, ld, i0, n);
     rc.store(cb, PL, n, lg);
     __syncthreads();
-    for (int i = 0; i < m; ++i) {
-        const double* cf = cb + (i & 1) * 5 * PL;
+    for (int i = i0; i < i1; ++i) {
+        const double* cf = cb + ((i - i0) & 1) * 5 * PL;
         // the next row of the solution and of the coefficients, requested before
         // this row's solve and used after it
         double un[kRwJ];
 #pragma unroll
         for (int k = 0; k < kRwJ; ++k) un[k] = 0.0;
-        if (i + 1 < m) {
-            rw_load_row(U + (i + 1) * rs, n, s, un);
-            rc.load(src, ld, i + 1, n);
-        }
+        if (i + 1 < m) rw_load_row(U + (i + 1) * rs, n, s, un);
+        if (i + 1 < i1) rc.load(src, ld, i + 1, n);
         const double vb = (b < a.B && !a.matvec && !a.term) ? a.V[(int64_t)b * m + i] : 0.0;
         // reciprocal ordering: the terminations' right-hand side at the last row
         const double* Vt = (a.term && !a.matvec && b < a.B && i == m - 1) ? a.V + (int64_t)b * n : nullptr;
@@ -975,7 +979,7 @@ __device__ __forceinline__ void residual_walk(const ResidualArgs& a, unsigned ch
             else
                 Ri[j] = 0.0f;
         }
-        if (i + 1 < m) rc.store(cb + ((i + 1) & 1) * 5 * PL, PL, n, lg);
+        if (i + 1 < i1) rc.store(cb + ((i + 1 - i0) & 1) * 5 * PL, PL, n, lg);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kRwJ; ++k) {
@@ -1016,18 +1020,19 @@ __device__ __forceinline__ void recover_walk(const RecoverArgs& a, unsigned char
     const double* const src[3] = {a.fr, a.ip, a.Gc};
     const int ld[3] = {n, n, n};
     RowCoeffs<3> rc;
+    const int i0 = (int)blockIdx.y * a.chunk, i1 = min(m, i0 + a.chunk);
     double uc[kRwJ];
-    rw_load_row(U, n, s, uc);
-    rc.load(src, ld, 0, n);
+    rw_load_row(U + i0 * rs, n, s, uc);
+    rc.load(src, ld, i0, n);
     rc.store(cb, PL, n, lg);
     __syncthreads();
     typedef double d2v __attribute__((ext_vector_type(2)));
-    for (int i = 0; i < m; ++i) {
-        const double* cf = cb + (i & 1) * 3 * PL;
+    for (int i = i0; i < i1; ++i) {
+        const double* cf = cb + ((i - i0) & 1) * 3 * PL;
         double un[kRwJ];
 #pragma unroll
         for (int k = 0; k < kRwJ; ++k) un[k] = 0.0;
-        if (i + 1 < m) {
+        if (i + 1 < i1) {
             rw_load_row(U + (i + 1) * rs, n, s, un);
             rc.load(src, ld, i + 1, n);
         }
@@ -1048,7 +1053,7 @@ __device__ __forceinline__ void recover_walk(const RecoverArgs& a, unsigned char
                 if (FULL || j < n) __builtin_nontemporal_store(d2v{w[padj(j, lg)], uc[k]}, reinterpret_cast<d2v*>(out + 2 * j));
             }
         }
-        if (i + 1 < m) rc.store(cb + ((i + 1) & 1) * 3 * PL, PL, n, lg);
+        if (i + 1 < i1) rc.store(cb + ((i + 1 - i0) & 1) * 3 * PL, PL, n, lg);
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kRwJ; ++k) uc[k] = un[k];
@@ -1143,17 +1148,29 @@ hipError_t xbk_launch_sweep_ir(const xbk::SweepArgs& a, hipStream_t s)
     return xbk::launch_sweep<float, true>(a, s);
 }
 
-hipError_t xbk_launch_residual(const xbk::ResidualArgs& a, hipStream_t s)
+// Rows per workgroup of the walkers: about two workgroups a CU in all, at least 16 rows
+// (a chunk reads the rows beside it again).
+static int walk_chunk(int m, int nslab)
 {
+    const int chunks = std::max(1, std::min(512 / std::max(1, 2 * nslab), m / 16));
+    return (m + chunks - 1) / chunks;
+}
+
+hipError_t xbk_launch_residual(const xbk::ResidualArgs& args, hipStream_t s)
+{
+    xbk::ResidualArgs a = args;
+    a.chunk = walk_chunk(a.m, a.nslab);
     const size_t lds = ((size_t)xbk::kRwCols + 2 * 5) * xbk::padded_len(a.n, xbk::kRwLanes) * sizeof(double);
-    hipLaunchKernelGGL(xbk::residual_kernel, dim3(2 * a.nslab), dim3(256), lds, s, a);
+    hipLaunchKernelGGL(xbk::residual_kernel, dim3(2 * a.nslab, (a.m + a.chunk - 1) / a.chunk), dim3(256), lds, s, a);
     return hipGetLastError();
 }
 
-hipError_t xbk_launch_recover(const xbk::RecoverArgs& a, hipStream_t s)
+hipError_t xbk_launch_recover(const xbk::RecoverArgs& args, hipStream_t s)
 {
-    if (a.slab_final == nullptr) return hipErrorInvalidValue;
+    if (args.slab_final == nullptr) return hipErrorInvalidValue;
+    xbk::RecoverArgs a = args;
+    a.chunk = walk_chunk(a.m, a.nslab);
     const size_t lds = ((size_t)xbk::kRwCols + 2 * 3) * xbk::padded_len(a.n, xbk::kRwLanes) * sizeof(double);
-    hipLaunchKernelGGL(xbk::recover_kernel, dim3(2 * a.nslab), dim3(256), lds, s, a);
+    hipLaunchKernelGGL(xbk::recover_kernel, dim3(2 * a.nslab, (a.m + a.chunk - 1) / a.chunk), dim3(256), lds, s, a);
     return hipGetLastError();
 }
