@@ -207,6 +207,15 @@ struct NSArgs {
     int max_iter;
 };
 
+// Newton-Schulz by column panels (ns_panel.hip): per chain two pivot blocks and first
+// iterates, and the iterates of the last two launches.
+struct NSPanelArgs {
+    NSArgs a;
+    void* S[2][2];
+    void* X[2][2];
+    void* Y[2][2];
+};
+
 // Crossbar blockIdx.y of a batch of one shape reads G + y m n and writes E, c, fr,
 // ip, q and Gc at y times one crossbar's size (gridDim.y = 1 for a plan).
 struct CondenseArgs {
@@ -361,6 +370,8 @@ hipError_t xbk_launch_factor(const xbk::GJArgs& a, bool fp32, hipStream_t s);
 hipError_t xbk_launch_ns_init(const xbk::NSArgs& a, hipStream_t s);
 hipError_t xbk_launch_ns_slots(const xbk::NSArgs& a, bool fp32, int chain, int first, int count, hipStream_t s);
 hipError_t xbk_launch_ns_finish(const xbk::NSArgs& a, int launched0, int launched1, int launched2, hipStream_t s);
+// one launch of schedule `chain` (-1: both chains) at n_p = 128 (ns_panel.hip)
+hipError_t xbk_launch_ns_panels(const xbk::NSPanelArgs& a, bool fp32, int chain, int slot, hipStream_t s);
 // whole factor of a plan with n_p = 64 (ns_chain.hip); report: a missed tolerance raises kErrConv
 hipError_t xbk_launch_ns_chains(const xbk::NSArgs& a, bool fp32, bool report, hipStream_t s);
 hipError_t xbk_launch_sweep(const xbk::SweepArgs& a, hipStream_t s);

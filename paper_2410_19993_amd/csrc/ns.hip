@@ -435,12 +435,13 @@ __device__ __forceinline__ bool ns_update(const NSArgs& a, const NSJob& job, con
     return fin;
 }
 
-// One slot of schedule `chain`: its current phase, spread over (n_p/32)^2
+// One slot of schedule `chain` (-1: both chains): its current phase, spread over (n_p/32)^2
 // workgroups (a 32x32 output tile each); workgroup 0 writes the next state.  A
 // finished schedule only carries its state over.
 template <typename T, int NT>
-__global__ __launch_bounds__(256) void ns_slot_kernel(NSArgs a, int chain, int slot)
+__global__ __launch_bounds__(256) void ns_slot_kernel(NSArgs a, int chain0, int slot)
 {
+    const int chain = chain0 < 0 ? (int)blockIdx.y : chain0;
     constexpr int tdim = 2 * NT;
     __shared__ __align__(16) T red[4 * 4 * 4 * 64];       // product partials [wave][output tile][item][lane]
     __shared__ double wmax[4];
@@ -545,7 +546,8 @@ hipError_t launch_slots_nt(const NSArgs& a, int chain, int first, int count, hip
 {
     constexpr int tiles = (2 * NT) * (2 * NT);
     for (int k = 0; k < count; ++k) {
-        hipLaunchKernelGGL((ns_slot_kernel<T, NT>), dim3(tiles), dim3(256), 0, s, a, chain, first + k);
+        hipLaunchKernelGGL((ns_slot_kernel<T, NT>), dim3(tiles, chain < 0 ? 2 : 1), dim3(256), 0, s, a, chain,
+                           first + k);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -556,8 +558,6 @@ template <typename T>
 hipError_t launch_slots(const NSArgs& a, int chain, int first, int count, hipStream_t s)
 {
     switch (a.n_p / 64) {
-        case 1: return launch_slots_nt<T, 1>(a, chain, first, count, s);
-        case 2: return launch_slots_nt<T, 2>(a, chain, first, count, s);
         case 3: return launch_slots_nt<T, 3>(a, chain, first, count, s);
         case 4: return launch_slots_nt<T, 4>(a, chain, first, count, s);
         case 5: return launch_slots_nt<T, 5>(a, chain, first, count, s);
@@ -578,7 +578,7 @@ hipError_t xbk_launch_ns_init(const xbk::NSArgs& a, hipStream_t s)
 
 hipError_t xbk_launch_ns_slots(const xbk::NSArgs& a, bool fp32, int chain, int first, int count, hipStream_t s)
 {
-    if (chain < 0 || chain > 2) return hipErrorInvalidValue;
+    if (chain < -1 || chain > 2) return hipErrorInvalidValue;
     return fp32 ? xbk::launch_slots<float>(a, chain, first, count, s)
                 : xbk::launch_slots<double>(a, chain, first, count, s);
 }

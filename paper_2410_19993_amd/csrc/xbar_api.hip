@@ -539,11 +539,15 @@ xbk::NSArgs ns_args(xbar_plan p)
     return a;
 }
 
+// Launches of a round or step at n_p > 64: one at n_p = 128 (ns_panel.hip), else three in
+// float64 and two in float32 (ns.hip).
+bool ns_panels(xbar_plan p) { return p->n_p == 128; }
+int ns_per_round(xbar_plan p) { return ns_panels(p) ? 1 : p->fp32() ? 2 : 3; }
+
 // Launch budget of a Newton-Schulz schedule that is not read back: the launches
 // it needed the last time they were read back (ns_slots_hint), plus a margin of
-// extra rounds (three launches each in float64, one two-launch step in float32)
-// for a conductance map whose rows need more.  The margin grows with the rounds
-// beyond one per row that the schedule needed then (k): rows that need one or two
+// extra rounds for a conductance map whose rows need more.  The margin grows with the
+// rounds beyond one per row that the schedule needed then (k): rows that need one or two
 // rounds make the count vary from map to map by about sqrt(k) rounds.  Launches
 // past a schedule's end only carry its final state over.
 int ns_budget(xbar_plan p, int c)
@@ -551,16 +555,39 @@ int ns_budget(xbar_plan p, int c)
     const int m = p->g.m, kt = m / 2;
     const int rows = c == 0 ? kt : c == 1 ? std::max(0, m - 1 - kt) : 1;
     if (rows == 0) return 0;
-    const int per_round = p->fp32() ? 2 : 3;
-    const double k = std::max(0.0, (p->ns_slots_hint[c] - 1) / (double)per_round - rows);
+    // beside the rounds: the form launch and, with panels, the one that sees the end
+    const int per_round = ns_per_round(p), other = ns_panels(p) ? 2 : 1;
+    const double k = std::max(0.0, (p->ns_slots_hint[c] - other) / (double)per_round - rows);
     const int margin = 4 + (int)std::ceil(0.5 * k + 4.0 * std::sqrt(k));
     return p->ns_slots_hint[c] + per_round * margin;
 }
 
-// Newton-Schulz factor on its device-driven schedule.  The two chains run on the
-// plan stream and the side stream (so that one chain's launches fill the matrix
-// cores while the other's start up or write out); schedule 2 (the twist) runs on
-// the plan stream once both have finished.
+hipError_t launch_ns(xbar_plan p, const xbk::NSArgs& a, int chain, int slot, hipStream_t s)
+{
+    if (!ns_panels(p)) return xbk_launch_ns_slots(a, p->fp32(), chain, slot, 1, s);
+    xbk::NSPanelArgs pa{};
+    pa.a = a;
+    for (int c = 0; c < 2; ++c) {
+        // (the Gauss-Jordan working blocks are free here)
+        pa.S[c][0] = p->d.ns_S[c];
+        pa.S[c][1] = p->d.S[c][0];
+        pa.Y[c][0] = p->d.ns_Q[c];
+        pa.Y[c][1] = p->d.S[c][1];
+        for (int k = 0; k < 2; ++k) pa.X[c][k] = p->d.ns_X[c][k];
+    }
+    return xbk_launch_ns_panels(pa, p->fp32(), chain, slot, s);
+}
+
+// Largest padded block whose two chains share their launches: a launch is then shorter
+// than its start, and two streams' launches only cost the host twice the time.
+// Microseconds a row of both chains, shared / two streams: n_p = 192 20.5 / 23.6, 256
+// 21.1 / 26.2, 320 24.2 / 29.6, 384 37.4 / 34.1, 512 42.5 / 41.3.
+constexpr int kNsShared = 320;
+
+// Newton-Schulz factor on its device-driven schedule.  Up to kNsShared the two chains
+// share their launches; larger blocks run them on the plan stream and the side stream (so
+// that one chain's launches fill the matrix cores while the other's start up or write
+// out).  Schedule 2 (the twist) runs on the plan stream once both have finished.
 //  - asynchronous (checked == false): each schedule gets its launch budget and
 //    nothing is read back, so the call can be captured into a graph; a finishing
 //    kernel raises kErrConv when a row missed its tolerance or a schedule ran out
@@ -576,6 +603,7 @@ hipError_t run_ns(xbar_plan p, bool checked, bool* failed)
     if (e != hipSuccess) return e;
     const int m = p->g.m, kt = m / 2;
     const int rows[3] = {kt, std::max(0, m - 1 - kt), 1};
+    const bool shared = p->n_p <= kNsShared, panels = ns_panels(p);
     hipStream_t on[3] = {p->stream, p->side, p->stream};
     int launched[3] = {0, 0, 0}, batch[3];
     int cap[3];
@@ -587,6 +615,7 @@ hipError_t run_ns(xbar_plan p, bool checked, bool* failed)
         else
             batch[c] = rows[c] == 0                ? 0
                        : p->ns_slots_hint[c] > 0 ? p->ns_slots_hint[c]
+                       : panels                  ? rows[c] + 8
                        : c == 2                  ? 2 * steps + 2
                                                  : rows[c] * 5 + 8;
     }
@@ -595,9 +624,10 @@ hipError_t run_ns(xbar_plan p, bool checked, bool* failed)
     // read every state back (through the plan stream, after the side stream's work)
     auto sync_states = [&]() -> hipError_t {
         hipError_t r;
-        if ((r = hipEventRecord(p->ev_join, p->side)) != hipSuccess ||
-            (r = hipStreamWaitEvent(p->stream, p->ev_join, 0)) != hipSuccess ||
-            (r = hipMemcpyAsync(st, p->d.ns_state, sizeof(st), hipMemcpyDeviceToHost, p->stream)) != hipSuccess ||
+        if (!shared && ((r = hipEventRecord(p->ev_join, p->side)) != hipSuccess ||
+                        (r = hipStreamWaitEvent(p->stream, p->ev_join, 0)) != hipSuccess))
+            return r;
+        if ((r = hipMemcpyAsync(st, p->d.ns_state, sizeof(st), hipMemcpyDeviceToHost, p->stream)) != hipSuccess ||
             (r = hipMemcpyAsync(&fail, p->d.flags + xbk::kNsFail, sizeof(int), hipMemcpyDeviceToHost,
                                 p->stream)) != hipSuccess)
             return r;
@@ -605,22 +635,26 @@ hipError_t run_ns(xbar_plan p, bool checked, bool* failed)
     };
     auto state_of = [&](int c) -> const xbk::NSState& { return st[3 * (launched[c] & 1) + c]; };
     // the side stream starts after the plan stream's work so far (E blocks, initial states)
-    if ((e = hipEventRecord(p->ev_fork, p->stream)) != hipSuccess ||
-        (e = hipStreamWaitEvent(p->side, p->ev_fork, 0)) != hipSuccess)
+    if (!shared && ((e = hipEventRecord(p->ev_fork, p->stream)) != hipSuccess ||
+                    (e = hipStreamWaitEvent(p->side, p->ev_fork, 0)) != hipSuccess))
         return e;
     for (int phase = 0; phase < 2; ++phase) {
         const int c0 = phase == 0 ? 0 : 2, c1 = phase == 0 ? 1 : 2;
         for (;;) {
             // interleave the two chains' launches so that both streams stay fed
             const int most = std::max(batch[c0], batch[c1]);
-            for (int k = 0; k < most; ++k)
+            if (shared && phase == 0) batch[0] = batch[1] = most;
+            for (int k = 0; k < most; ++k) {
+                if (shared && phase == 0) {
+                    if ((e = launch_ns(p, a, -1, launched[0] + k, p->stream)) != hipSuccess) return e;
+                    continue;
+                }
                 for (int c = c0; c <= c1; ++c)
-                    if (k < batch[c] && (e = xbk_launch_ns_slots(a, p->fp32(), c, launched[c] + k, 1, on[c])) !=
-                                            hipSuccess)
-                        return e;
+                    if (k < batch[c] && (e = launch_ns(p, a, c, launched[c] + k, on[c])) != hipSuccess) return e;
+            }
             for (int c = c0; c <= c1; ++c) launched[c] += batch[c];
             if (!checked) {
-                if (phase == 0 &&
+                if (phase == 0 && !shared &&
                     ((e = hipEventRecord(p->ev_join, p->side)) != hipSuccess ||
                      (e = hipStreamWaitEvent(p->stream, p->ev_join, 0)) != hipSuccess))
                     return e;
@@ -638,7 +672,7 @@ hipError_t run_ns(xbar_plan p, bool checked, bool* failed)
                     continue;
                 }
                 const int left = c == 0 ? kt - s.row : c == 1 ? s.row - kt : 1;
-                batch[c] = std::min(std::max(8, 5 * left + 4), cap[c] - launched[c]);
+                batch[c] = std::min(panels ? left + 4 : std::max(8, 5 * left + 4), cap[c] - launched[c]);
             }
             if (over) {
                 *failed = true;

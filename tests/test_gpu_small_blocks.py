@@ -43,3 +43,26 @@ def test_small_blocks_of_a_wide_crossbar(m, n):
     I, nv, (st, _) = gpu_solve(wl.G, wl.V, wl.geom, ordering="smaller")
     assert st == 0
     assert rel_err(I, ref.currents).max() <= TOL_FP64 and node_rel_err(nv, ref.node_v).max() <= TOL_FP64
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir"])
+@pytest.mark.parametrize("m,n", [(1, 65), (2, 128), (3, 113), (4, 81), (9, 127), (12, 96), (1, 129), (2, 192), (5, 256),
+                                 (4, 320)])
+def test_shared_launch_factor_matches_oracle(m, n, precision):
+    """Factors whose two chains share their launches (column panels at 65 to 128 columns,
+    the slot schedule to 320): chains of no, one and a few rows, and devices strong enough
+    to need more than one round in a row."""
+    for strong in (False, True):
+        wl = workloads.random_crossbar(m, n, 5, 9700 + 64 * m + n, r_wl=1.5, r_bl=3.0, r_src=40.0, r_sense=60.0)
+        if strong:
+            wl.G[:] *= 20.0
+        log(f"case {wl.name} {precision} strong={strong}")
+        ref = oracle.solve_workload(wl)
+        tol = TOL_FP64 if precision == "fp64" else TOL_IR
+        outs = []
+        for method in ("auto", "checked", "gj"):
+            I, nv, (st, info) = gpu_solve(wl.G, wl.V, wl.geom, precision, ordering="rows", factor_method=method)
+            assert st == 0 and 0.0 < info.min_pivot
+            assert rel_err(I, ref.currents).max() <= tol and node_rel_err(nv, ref.node_v).max() <= tol
+            outs.append(I)
+        assert np.array_equal(outs[0], outs[1])
