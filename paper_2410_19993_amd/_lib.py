@@ -128,6 +128,9 @@ def lib() -> ctypes.CDLL:
         L.xbar_sg_readout_loss.argtypes = [i32, i32, i32, vp, vp, f64, vp, vp, vp]
         L.xbar_sg_adam.argtypes = [i64, vp, vp, vp, vp, f64, f64, f64, f64, i32, vp]
         L.xbar_sg_predict.argtypes = [i32, i32, i32, vp, vp, vp, vp, vp, vp]
+        L.xbar_sg_infer_workspace_bytes.argtypes = [i32, i32, i32, i32, i32]
+        L.xbar_sg_infer_workspace_bytes.restype = i64
+        L.xbar_sg_infer_bf16.argtypes = [i32, i32, i32, i32, i32, vp, vp, vp, vp, vp, i64, vp, vp, vp]
         L.xbar_sg_targets.argtypes = [i32, i32, vp, vp, vp, vp]
         L.xbar_sg_calib_ratios.argtypes = [i32, i32, vp, vp, vp, vp, vp]
         L.xbar_sg_route.argtypes = [i32, i32, i32, vp, vp, vp, vp, f64, f64, vp, vp]
@@ -141,7 +144,7 @@ def lib() -> ctypes.CDLL:
                   "xbar_sg_conv_backward_data", "xbar_sg_conv_backward_weight",
                   "xbar_sg_conv_backward_weight_noalloc", "xbar_sg_conv_forward_bf16",
                   "xbar_sg_conv_backward_data_bf16", "xbar_sg_conv_backward_weight_bf16", "xbar_sg_readout_loss",
-                  "xbar_sg_adam", "xbar_sg_predict", "xbar_sg_targets", "xbar_sg_calib_ratios", "xbar_sg_route"):
+                  "xbar_sg_adam", "xbar_sg_predict", "xbar_sg_infer_bf16", "xbar_sg_targets", "xbar_sg_calib_ratios", "xbar_sg_route"):
             getattr(L, f).restype = ctypes.c_int
         _lib = L
     return _lib
@@ -322,6 +325,16 @@ def xbar_sg_adam(p, g, m1, m2, lr, b1, b2, eps, t, stream=None) -> None:
 def xbar_sg_predict(B, m, n, Y, G, V, I, est=None, stream=None) -> None:
     _check("xbar_sg_predict", lib().xbar_sg_predict(B, m, n, _ptr(Y), _ptr(G), _ptr(V), _ptr(I), _ptr(est),
                                                     _s(stream)))
+
+
+def xbar_sg_infer_workspace_bytes(B, m, n, C, depth) -> int:
+    return int(lib().xbar_sg_infer_workspace_bytes(B, m, n, C, depth))
+
+
+def xbar_sg_infer_bf16(B, m, n, C, depth, G, V, r, params, work, I, est=None, stream=None) -> None:
+    _check("xbar_sg_infer_bf16", lib().xbar_sg_infer_bf16(B, m, n, C, depth, _ptr(G), _ptr(V), _ptr(r), _ptr(params),
+                                                          _ptr(work), int(work.numel()), _ptr(I), _ptr(est),
+                                                          _s(stream)))
 
 
 def xbar_sg_targets(S, n, I, I0, delta, stream=None) -> None:

@@ -86,6 +86,7 @@ class Surrogate:
         ws = max(_lib.xbar_sg_workspace_floats(self.dims[k], self.dims[k + 1]) for k in range(self.L))
         self.work = torch.empty(ws, dtype=torch.float32, device="cuda")
         self._buf_shape = None
+        self._infer_work = None
         self._solvers = {}
         self.kappa = 1.0
 
@@ -208,6 +209,15 @@ class Surrogate:
         _check_tensor("out", out, (B, n))
         if est is not None:
             _check_tensor("est", est, (B, n))
+        # the bfloat16 network in one pass over the maps where the call takes its sizes,
+        # else layer by layer
+        need = _lib.xbar_sg_infer_workspace_bytes(B, m, n, self.C, self.L) if self._bf16 else -1
+        if need >= 0:
+            if self._infer_work is None or self._infer_work.numel() < need:
+                self._infer_work = torch.empty(need, dtype=torch.uint8, device="cuda")
+            _lib.xbar_sg_infer_bf16(B, m, n, self.C, self.L, G, V, r, self.params, self._infer_work, out, est,
+                                    self._stream())
+            return out
         self.forward(G, V, r)
         _lib.xbar_sg_predict(B, m, n, self.Y, G, V, out, est, self._stream())
         return out

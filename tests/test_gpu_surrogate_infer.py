@@ -1,0 +1,51 @@
+"""Surrogate inference in one pass (xbar_sg_infer_bf16) against the layer-by-layer path:
+tile edges, maps smaller than a tile, every rounding of the channel count and every depth.
+
+The last map has the same bits in both, so currents and estimates may differ only by the
+rounding of float64 sums over at most m rows: relative tolerance 4 m eps (1 + S), with S
+the largest mean absolute map value over |1 + yhat| (cancellation in 1 + yhat), plus the
+exponential's amplification 2 of the estimate's own sum.
+"""
+import numpy as np
+import pytest
+
+from tests.gpu_util import log
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("depth,C", [(2, 1), (2, 32), (3, 7), (3, 16), (4, 8), (4, 20), (4, 32), (5, 17), (5, 32)])
+@pytest.mark.parametrize("B,m,n", [(1, 1, 1), (3, 7, 33), (2, 8, 32), (5, 17, 100), (2, 40, 65), (64, 128, 128)])
+def test_one_pass_inference_matches_layers(B, m, n, depth, C):
+    import torch
+
+    from paper_2410_19993_amd import _lib
+    from paper_2410_19993_amd.surrogate import Surrogate
+    rng = np.random.default_rng(1000 * depth + 10 * C + m + n)
+    log(f"case infer B={B} {m}x{n} depth={depth} C={C}")
+    G = torch.from_numpy(np.exp(rng.uniform(np.log(1e-6), np.log(1e-4), (B, m, n)))).cuda()
+    V = torch.from_numpy(rng.uniform(0.0, 0.5, (B, m))).cuda()
+    r = torch.from_numpy(rng.uniform(1.0, 5.0, B)).cuda()
+    net = Surrogate(channels=C, seed=3, depth=depth, zero_last=False)
+    net.params += 0.01 * torch.from_numpy(rng.normal(size=net.params.numel()).astype(np.float32)).cuda()
+    assert _lib.xbar_sg_infer_workspace_bytes(B, m, n, C, depth) > 0
+    est = torch.empty((B, n), dtype=torch.float64, device="cuda")
+    I = net.predict(G, V, r, est=est).cpu().numpy()
+    est = est.cpu().numpy()
+    Y = net.forward(G, V, r)
+    I2 = torch.empty((B, n), dtype=torch.float64, device="cuda")
+    e2 = torch.empty_like(I2)
+    _lib.xbar_sg_predict(B, m, n, Y, G, V, I2, e2, net._stream())
+    I2, e2 = I2.cpu().numpy(), e2.cpu().numpy()
+    Yh = Y.cpu().numpy().astype(np.float64)
+    one = np.abs(1.0 + Yh[:, 0].mean(axis=1))
+    S = np.abs(Yh).mean(axis=2).max(axis=1) / one
+    tol = 4 * m * np.finfo(float).eps * (1 + S)
+    assert np.all(np.abs(I - I2) <= tol * np.abs(I2) + 1e-300)
+    assert np.all(np.abs(est - e2) <= 2 * (tol + 4 * m * np.finfo(float).eps * np.abs(Yh).mean(axis=2).max(axis=1)) * e2)
+
+
+def test_sizes_outside_the_one_pass_call():
+    from paper_2410_19993_amd import _lib
+    for args in ((1, 8, 8, 8, 6), (1, 8, 8, 33, 4), (1, 2049, 8, 8, 4), (0, 8, 8, 8, 4), (1, 8, 8, 8, 1)):
+        assert _lib.xbar_sg_infer_workspace_bytes(*args) == -1
