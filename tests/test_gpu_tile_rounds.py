@@ -1,0 +1,42 @@
+"""Batched small crossbars: the Newton-Schulz rounds and the elimination of a row.
+
+A row's inverse is found from the row before's by one to three rounds, or by elimination
+where the rows differ too much (and in the first row).  Devices of 1 to 100 uS take one
+round, twenty times stronger ones two, alternating rows two and an elimination at the
+last row; every third row of strong devices is eliminated and the row after it starts
+from that inverse.  Shapes: both sides of each padded block size, of a segment of eight
+columns, of the 32 rows whose chains are walked together, and of the groups of 16
+vectors a wave owns.
+
+Against the oracle with the float64 tolerance of every solve (1e-10).
+"""
+import numpy as np
+import pytest
+
+import oracle
+from tests.gpu_util import TOL_FP64, log, rel_err
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("kind", ["weak", "strong", "alternating", "third"])
+@pytest.mark.parametrize("m,n,B", [(1, 64, 16), (2, 9, 1), (9, 8, 129), (12, 1, 17), (31, 16, 64), (32, 17, 65),
+                                   (33, 31, 256), (12, 32, 128), (34, 33, 15), (65, 64, 256), (7, 57, 100)])
+def test_rounds_and_elimination_match_oracle(m, n, B, kind):
+    import torch
+
+    import paper_2410_19993_amd as xb
+    log(f"case tiles {m}x{n} B={B} {kind}")
+    rng = np.random.default_rng(100 * m + n)
+    G = np.exp(rng.uniform(np.log(1e-6), np.log(1e-4), (2, m, n)))
+    if kind == "strong":
+        G *= 20.0
+    elif kind == "alternating":
+        G[:, 1::2] *= 300.0
+    elif kind == "third":
+        G[:, 2::3] *= 2e4
+    V = rng.uniform(0.0, 0.5, (2, B, m))
+    r = (1.5, 3.0, 40.0, 60.0)
+    I = xb.tiles_currents(torch.from_numpy(G).cuda(), torch.from_numpy(V).cuda(), *r).cpu().numpy()
+    for t in range(2):
+        assert rel_err(I[t], oracle.solve(G[t], V[t], *r).currents).max() <= TOL_FP64
