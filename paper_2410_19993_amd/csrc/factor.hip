@@ -752,6 +752,14 @@ __device__ inline GJSlot gj_col_slot(int nb, int nj, int batch, int scol)
     return s;
 }
 
+// Whether a launch takes column workgroups: they form X once where nb tile workgroups
+// each form it, but walk the column's tiles one after another, so they pay only once the
+// tile workgroups fill the chip four times over.  Factor and sweep of 64 vectors, column
+// against tile workgroups: 256 x 256, 12 crossbars (384 tile workgroups) 21.2 against
+// 18.0 ms, 48 (1536) 29.8 against 28.9; 192 x 192, 40 (720) 12.4 against 11.7, 80 (1440)
+// 17.9 against 19.6.
+inline bool gj_cols(int nj, int nb, int batch) { return nb >= 3 && (int64_t)nj * batch * nb * nb > 1024; }
+
 inline dim3 gj_col_grid(int nj, int nb, int batch)
 {
     return dim3((unsigned)(8 * ((nj * batch + 7) / 8) * nb));
@@ -909,7 +917,7 @@ hipError_t launch_factor(GJArgs a, hipStream_t s)
             f.job[nj].next = (m - 2 - st > kt) ? m - 2 - st : -1;
             ++nj;
         }
-        const bool cols = nj * a.batch >= 8 && nb >= 3;
+        const bool cols = gj_cols(nj, nb, a.batch);
         for (int k = 0; k < nb; ++k) {
             launch_step<T>(f, nj, st, k, cols, s);
             if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -925,7 +933,7 @@ hipError_t launch_factor(GJArgs a, hipStream_t s)
     hipLaunchKernelGGL(gj_form_kernel<T>, gj_grid(1, tiles, a.batch), dim3(256), 0, s, f, 1);
     if ((e = hipGetLastError()) != hipSuccess) return e;
     for (int k = 0; k < nb; ++k) {
-        launch_step<T>(f, 1, 0, k, a.batch >= 8 && nb >= 3, s);
+        launch_step<T>(f, 1, 0, k, gj_cols(1, nb, a.batch), s);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     return hipSuccess;

@@ -40,3 +40,26 @@ def test_rounds_and_elimination_match_oracle(m, n, B, kind):
     I = xb.tiles_currents(torch.from_numpy(G).cuda(), torch.from_numpy(V).cuda(), *r).cpu().numpy()
     for t in range(2):
         assert rel_err(I[t], oracle.solve(G[t], V[t], *r).currents).max() <= TOL_FP64
+
+
+@pytest.mark.parametrize("count,m,n", [(57, 4, 130), (58, 4, 130), (33, 5, 200)])
+def test_column_and_tile_workgroups_give_the_same_bits(count, m, n):
+    """The batched block factor on both sides of its rule (1024 tile workgroups a launch):
+    every crossbar of the batch as if it were alone."""
+    import torch
+
+    from paper_2410_19993_amd.tiles import TileBatch, TileConfig
+    rng = np.random.default_rng(count + n)
+    G = torch.from_numpy(np.exp(rng.uniform(np.log(1e-6), np.log(1e-4), (count, m, n)))).cuda()
+    V = torch.from_numpy(rng.uniform(0.0, 0.5, (count, 5, m))).cuda()
+    r = (1.5, 3.0, 40.0, 60.0)
+
+    def run(G, V):
+        batch = TileBatch([(m, n, G.shape[0], 5)], *r, configs=[TileConfig("pipeline")], streams=1)
+        out = batch.run([G], [V])[0].cpu().numpy()
+        batch.close()
+        return out
+    out = run(G, V)
+    for t in (0, 7, 8, count - 1):
+        assert np.array_equal(run(G[t:t + 1].contiguous(), V[t:t + 1].contiguous())[0], out[t])
+    assert rel_err(out[1], oracle.solve(G[1].cpu().numpy(), V[1].cpu().numpy(), *r).currents).max() <= TOL_FP64
