@@ -124,7 +124,8 @@ __global__ void tiles_clear_kernel(int* flags, unsigned long long* diag, int* ba
 struct xbar_tiles_s {
     std::vector<xbar_tile_class> cls;
     std::vector<PipeBuffers> pipe;
-    std::vector<int> order;              // classes, most work first
+    std::vector<int> order;              // classes, longest first
+    std::vector<int> lane;               // each class's stream
     double g_wl = 0, g_bl = 0, g_src = 0, g_sense = 0;
     hipStream_t stream = nullptr;
     std::vector<hipStream_t> side;
@@ -156,11 +157,26 @@ void tiles_free(xbar_tiles t)
     t->fork = nullptr;
 }
 
-// the class's work in flops (the method's count): factor m n^3, currents-only
-// forward sweep 2 m n^2 per vector
-double class_work(const xbar_tile_class& c)
+// A class's expected time alone on the device, in microseconds: its chain of rows, and its
+// flops (factor m n^3, currents-only sweep 2 m n^2 per vector) at 30 TFLOP/s.  The chains'
+// step times are measured: one workgroup 20, 7 or 4 us a row (blocks of 64, 32, 16); the
+// pipeline 24 us a block column of two rows and, in the sweep, 0.042 n_p us a row and side
+// (12 crossbars of 256 x 256 with 256 vectors: 17 ms expected, 18 measured; 24 of
+// 128 x 128: 4.7 and 4.5; 32 of 128 x 64: 2.8 and 2.6).  Flops alone put a chain of many
+// rows that leaves most of the chip idle behind a short one.
+double class_time(const xbar_tile_class& c)
 {
-    return (double)c.count * ((double)c.m * c.n * c.n * c.n + 2.0 * c.m * c.n * c.n * c.B);
+    const double m = c.transpose ? c.n : c.m, n = c.transpose ? c.m : c.n, B = c.transpose ? c.n : c.B;
+    const double flops = c.count * (m * n * n * n + 2.0 * m * n * n * B);
+    double chain;
+    if (c.method == XBAR_TILE_ONE_WG) {
+        const int block = c.block != 0 ? c.block : n <= 16 ? 16 : n <= 32 ? 32 : 64;
+        chain = m * (block == 64 ? 20.0 : block == 32 ? 7.0 : 4.0);
+    } else {
+        const double nb = std::ceil(n / 64.0);
+        chain = 0.5 * m * nb * 24.0 + 1.5 * m * 0.042 * 64.0 * nb;
+    }
+    return chain + flops / 30e6;
 }
 
 hipError_t run_pipe(xbar_tiles t, int k, const Inner& in, const double* G, const double* V, double* I, hipStream_t s)
@@ -380,7 +396,17 @@ xbar_status xbar_tiles_create(const xbar_tile_class* classes, int32_t nclasses, 
     t->order.resize(nclasses);
     for (int k = 0; k < nclasses; ++k) t->order[k] = k;
     std::stable_sort(t->order.begin(), t->order.end(),
-                     [&](int a, int b) { return class_work(t->cls[a]) > class_work(t->cls[b]); });
+                     [&](int a, int b) { return class_time(t->cls[a]) > class_time(t->cls[b]); });
+    // longest first, each to the stream that ends earliest so far (the classes of 32x32,
+    // 64x128, 128x64, 128x128, 256x128 and 256x256 on two streams: 21.9 ms, 26.2 with the
+    // streams taken in turn)
+    t->lane.resize(nclasses);
+    std::vector<double> ends(streams, 0.0);
+    for (int k : t->order) {
+        const int j = (int)(std::min_element(ends.begin(), ends.end()) - ends.begin());
+        t->lane[k] = j;
+        ends[j] += class_time(t->cls[k]);
+    }
     *out = t;
     return XBAR_OK;
 }
@@ -396,10 +422,8 @@ xbar_status xbar_tiles_run(xbar_tiles t, const double* const* G, const double* c
     if (hipEventRecord(t->fork, t->stream) != hipSuccess) return XBAR_ERR_DEVICE;
     for (int j = 0; j < ns; ++j)
         if (hipStreamWaitEvent(t->side[j], t->fork, 0) != hipSuccess) return XBAR_ERR_DEVICE;
-    // classes round-robin over the streams, most work first
-    for (int j = 0; j < nc; ++j) {
-        const int k = t->order[j];
-        hipStream_t s = t->side[j % ns];
+    for (int k : t->order) {
+        hipStream_t s = t->side[t->lane[k]];
         const hipError_t e = run_class(t, k, G[k], V[k], I[k], s);
         if (e != hipSuccess) {
             (void)hipGetLastError();
