@@ -209,14 +209,17 @@ xbar_status xbar_currents(xbar_plan plan, double* I);
  * that is linear in the source voltages (Sec. II.A, Eqs. 5-7), so the currents
  * of any input vector are I[b][j] = sum_i V[b][i] T[i][j]: see
  * xbar_transfer_apply.  How T is computed from the plan's factorization:
- *  - XBAR_FP64 plans whose max_batch, rounded up to 16, is at least the padded
+ *  - XBAR_FP64 plans in row ordering with max_batch >= m, of at most 256 rows (1024
+ *    if n <= 128), and every other mode or ordering: by solving the m unit inputs,
+ *    min(max_batch, m) of them per xbar_solve_batch, without node voltages, in the
+ *    plan's precision mode;
+ *  - other XBAR_FP64 plans whose max_batch, rounded up to 16, is at least the padded
  *    block size (n rounded up to 64): by block recurrences.  The condensed
  *    system is symmetric, so row i of T is g_sense W_i c_i, with W_i the
  *    transposed block row i of the inverse applied to identity blocks at the
  *    last row; the W_i follow from the factorization by the substitution
  *    recurrences on whole blocks (about m dependent block products);
- *  - otherwise: by solving the m unit inputs, min(max_batch, m) of them per
- *    xbar_solve_batch, without node voltages, in the plan's precision mode.
+ *  - otherwise: by solving the unit inputs as above.
  *   T  device, [m][n] row-major, amperes per volt; caller-owned.
  * Requires a prior xbar_factor (XBAR_ERR_STATE otherwise).  Uses the plan's
  * batch workspace: the result of an earlier xbar_solve_batch is dropped and

@@ -47,7 +47,7 @@ struct Buffers {
     int* slab_done = nullptr;                // [nslab]
     int* slab_final = nullptr;               // [nslab]
     double* Vunit = nullptr;                 // [tr_rows][m]: unit inputs of xbar_transfer (plans
-                                             // without the block form only)
+                                             // that solve them only)
     // Krylov refinement (XBAR_BF16_GMRES_IR): Arnoldi basis v_0..v_k and preconditioned
     // directions z_0..z_{k-1} (panels), a zero panel, reduction partials, the Hessenberg
     // matrices [k+1][k][Bp], beta [Bp], y [k][Bp] and Gram-Schmidt coefficients [k+1][Bp]
@@ -221,9 +221,23 @@ bool reciprocal_is_faster(int m, int n)
     return (double)n * row_us(m) < (double)m * row_us(n);
 }
 
+// Whether the plan's batch workspace holds the block recurrences of T.
 bool transfer_blocks_fit(xbar_plan p)
 {
     return !p->rev && p->prec == XBAR_FP64 && (int64_t)p->nslab_max * 16 >= p->n_p;
+}
+
+// Whether T is built by them (else by solving the unit inputs).  The recurrences are
+// m - 1 launches of n_p^3 products; the m unit inputs in one batch take the sweeps'
+// launches or, to 128 columns, two, and their products grow with m.  Blocks against
+// solves, in ms: 512 x 512 6.4 and 7.3, 384 x 512 4.8 and 5.3, 384 x 256 2.5 and 2.5,
+// 320 x 512 4.1 and 4.3, 256 x 512 3.3 and 2.8, 256 x 192 1.36 and 1.22, 64 x 512 0.85 and
+// 0.49, 1024 x 128 4.6 and 3.6, 512 x 64 1.9 and 0.65, 17 x 40 0.092 and 0.036.  Split over
+// several batches the solves repeat their launches.
+bool transfer_by_recurrence(xbar_plan p)
+{
+    const bool solves = p->tr_rows == p->og.m && (p->og.m <= 256 || (p->n_p <= 128 && p->og.m <= 1024));
+    return transfer_blocks_fit(p) && !solves;
 }
 
 // Reciprocal crossbar of the given m x n one (n > m): Gr [n][m], Gr[i][j] = G[m-1-j][n-1-i].
@@ -400,7 +414,7 @@ xbar_status xbar_create_ordered(const xbar_geometry* geom, xbar_precision prec, 
     A((void**)&d.ns_state, 6 * sizeof(xbk::NSState));
     if (xbk_step_slabs(p->n_p, p->fp32()) > 0)
         A(&d.ysteps, 4 * (int64_t)std::min(p->nslab_max, xbk_step_slabs(p->n_p, p->fp32())) * 16 * n_p * es);
-    if (!transfer_blocks_fit(p)) A((void**)&d.Vunit, (int64_t)p->tr_rows * og.m * 8);
+    if (!transfer_by_recurrence(p)) A((void**)&d.Vunit, (int64_t)p->tr_rows * og.m * 8);
     if (rev) {
         A((void**)&d.Grev, m * n * 8);
         A((void**)&d.nv_rev, (int64_t)max_batch * 2 * m * n * 8);
@@ -753,7 +767,7 @@ bool overlaps(const void* a, int64_t a_bytes, const void* b, int64_t b_bytes)
 xbar_status transfer_by_unit_solves(xbar_plan p, double* T)
 {
     const int m = p->og.m, n = p->og.n;                  // the crossbar as given
-    const bool timing = p->timing;
+    const bool timing = p->timing, backerr = p->backerr_valid;
     p->timing = false;                     // the unit solves are not counted as sweeps
     xbar_status st = XBAR_OK;
     for (int i0 = 0; i0 < m && st == XBAR_OK; i0 += p->tr_rows) {
@@ -772,6 +786,7 @@ xbar_status transfer_by_unit_solves(xbar_plan p, double* T)
             st = XBAR_ERR_DEVICE;
     }
     p->timing = timing;
+    if (transfer_blocks_fit(p)) p->backerr_valid = backerr;   // as after the recurrences
     return st;
 }
 
@@ -1121,7 +1136,7 @@ xbar_status xbar_transfer(xbar_plan p, double* T)
     if (p == nullptr || T == nullptr) return XBAR_ERR_ARG;
     if (p->state < kFactored) return XBAR_ERR_STATE;
     if (!set_device(p)) return XBAR_ERR_DEVICE;
-    const xbar_status st = transfer_blocks_fit(p) ? transfer_by_blocks(p, T) : transfer_by_unit_solves(p, T);
+    const xbar_status st = transfer_by_recurrence(p) ? transfer_by_blocks(p, T) : transfer_by_unit_solves(p, T);
     // the batch workspace no longer holds a caller's batch
     p->state = kFactored;
     p->last_B = 0;

@@ -68,3 +68,26 @@ def test_refinement_by_steps(m, n, B, seed):
     assert stb == 0 and infob.ir_iters == info.ir_iters
     k = B // 16 * 16                   # a slab stops as a whole: compare whole ones
     assert np.array_equal(Ib[:k], I[:k]) and np.array_equal(nvb[:k], nv[:k])
+
+
+@pytest.mark.parametrize("m,n", [(1, 64), (16, 129), (256, 70), (257, 64), (257, 130)])
+def test_transfer_by_either_route(m, n):
+    """T by unit solves (one batch holds them, few rows or columns) and by the block
+    recurrences (the last shape, and a plan whose batch is one row short): both against
+    the oracle, and the last solve's backward error is reported after either."""
+    import torch
+
+    import paper_2410_19993_amd as xb
+    wl = workloads.random_crossbar(m, n, 3, 8800 + m + n, r_wl=1.5, r_bl=3.0, r_src=40.0, r_sense=60.0)
+    g = wl.geom
+    ref = oracle.solve(wl.G, np.eye(m), g.r_wl, g.r_bl, g.r_src, g.r_sense).currents
+    for max_batch in (max(m, 256), max(m - 1, 64)):
+        log(f"case transfer {m}x{n} max_batch={max_batch}")
+        with xb.Plan(m, n, g.r_wl, g.r_bl, g.r_src, g.r_sense, "fp64", max_batch=max_batch, ordering="rows") as p:
+            p.assemble(torch.from_numpy(wl.G).cuda())
+            p.factor()
+            before = p.info()[1].max_backward_err
+            T = p.transfer().cpu().numpy()
+            st, info = p.info()
+        assert st == 0 and info.max_backward_err == before
+        assert rel_err(T, ref).max() <= TOL_FP64
