@@ -348,7 +348,8 @@ xbar_status xbar_get_info(xbar_plan plan, xbar_info* info);
 /*
  * How xbar_factor inverts the pivot blocks of the block LU.
  *   XBAR_FACTOR_AUTO (default): Newton-Schulz iteration on the matrix cores, on
- *       a schedule driven by the device.  The first factorization of a plan
+ *       a schedule driven by the device.  To 64 columns the schedule's length is
+ *       known and nothing is read back.  Above, the first factorization of a plan
  *       reads the schedule back (it synchronises the plan's stream) and so
  *       learns how many launches each of its three schedules needs; later ones
  *       are asynchronous and capturable: each schedule gets that many launches
@@ -394,8 +395,8 @@ xbar_status xbar_debug_shift_pivots(xbar_plan plan, double shift);
  * Phase timing, measured with HIP events recorded on the plan's stream
  * around each phase of the calls above (only while enabled): one interval
  * per xbar_assemble (condense), per xbar_factor (all its kernels), per
- * xbar_solve_batch (its substitution sweeps; in FP64 mode that is exactly
- * one kernel, the sweep with the word-line recovery fused) and per
+ * xbar_solve_batch (its substitution sweeps with, in FP64 mode, the word-line
+ * recovery: one kernel for large batches, several for small ones) and per
  * word-line recovery launch of the IR modes; inside the IR modes' solve,
  * also one interval per float32 sweep launch and per float64 residual
  * launch.  Times are accumulated milliseconds; *_launches count the

@@ -33,9 +33,11 @@
 // (factor.hip).
 //
 // The schedule is driven by the device.  The two chains are independent until
-// the twist, so each runs on a stream of its own, and a third schedule inverts
-// the twist block once both have finished; the launches of one chain then fill
-// the matrix cores while the other's are starting up or writing out.  Each
+// the twist, and a third schedule inverts the twist block once both have finished.
+// Above 320 columns each chain runs on a stream of its own: the launches of one then
+// fill the matrix cores while the other's are starting up or writing out.  Below, the
+// chains share their launches.  (Blocks to 64 columns: ns_chain.hip; to 128:
+// ns_panel.hip.)  Each
 // launch (slot) does one phase of its schedule (the form, or one launch of a
 // round) and hands the next state to the following launch, so a converged row
 // costs no further launches.  The launch that finishes a row also

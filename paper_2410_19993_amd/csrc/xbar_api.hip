@@ -197,9 +197,6 @@ void free_all(xbar_plan p)
 
 bool set_device(xbar_plan p) { return hipSetDevice(p->device) == hipSuccess; }
 
-// The block form of xbar_transfer keeps m FRG blocks of n_p x n_p in the sweep workspace
-// (float64 plans whose max_batch, rounded up to 16, is at least n_p); other plans solve
-// unit inputs and hold a staging buffer for them.
 // Cost model of the choice between the two orderings of an m x n crossbar with n > m.
 // A simulation (assembly, factor, solve) walks the chain of row blocks in sequence,
 // at about t(n_p) microseconds per row for the padded block size n_p; measured on
@@ -207,7 +204,9 @@ bool set_device(xbar_plan p) { return hipSetDevice(p->device) == hipSuccess; }
 // and grows beyond: t = 14, 15, 22, 30, 42, 55, 67, 80 for n_p = 64 .. 512.  Rows:
 // m t(pad(n)); reciprocal: n t(pad(m)).  With it, among the wide shapes up to 256 x 512
 // the reciprocal wins at 128 x 512 and 256 x 512 and loses at every smaller or narrower
-// one, as the measurements did.
+// one, as the measurements did.  (They were taken with three launches a row at every
+// size; a row of a small batch is now 1 to 28 us.  The line stays where callers know it:
+// the choice sets a plan's block size, and at large batches the flops decide alike.)
 double row_us(int n)
 {
     const int n_p = 64 * ((n + 63) / 64);
@@ -221,7 +220,8 @@ bool reciprocal_is_faster(int m, int n)
     return (double)n * row_us(m) < (double)m * row_us(n);
 }
 
-// Whether the plan's batch workspace holds the block recurrences of T.
+// Whether the plan's batch workspace holds the block recurrences of T (m FRG blocks of
+// n_p x n_p).
 bool transfer_blocks_fit(xbar_plan p)
 {
     return !p->rev && p->prec == XBAR_FP64 && (int64_t)p->nslab_max * 16 >= p->n_p;
