@@ -76,9 +76,15 @@ __global__ void clear_slabs_kernel(int* done, double* dnorm, unsigned long long*
     }
 }
 
-__global__ void clear_flags_kernel(int* f)
+// The flags and diagnostics of a new assembly.  One launch: a small crossbar's pass is
+// its launches (16 x 16 with 8 vectors).
+__global__ void clear_state_kernel(int* f, unsigned long long* diag)
 {
     if (threadIdx.x < xbk::kNumFlags) f[threadIdx.x] = 0;
+    if (threadIdx.x == 0) {
+        diag[xbk::kDiagMinPivot] = xbk::kPivotKeyInf;
+        diag[xbk::kDiagBackErr] = 0ull;
+    }
 }
 
 bool finite_pos(double x) { return std::isfinite(x) && x > 0.0; }
@@ -447,8 +453,8 @@ xbar_status xbar_create_ordered(const xbar_geometry* geom, xbar_precision prec, 
         delete p;
         return st;
     }
-    hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, p->stream, d.flags);
-    if (hipGetLastError() != hipSuccess || xbk_launch_reset_diag(d.diag, 3, p->stream) != hipSuccess ||
+    hipLaunchKernelGGL(clear_state_kernel, dim3(1), dim3(64), 0, p->stream, d.flags, d.diag);
+    if (hipGetLastError() != hipSuccess ||
         hipStreamCreateWithFlags(&p->side, hipStreamNonBlocking) != hipSuccess ||
         hipEventCreateWithFlags(&p->ev_fork, hipEventDisableTiming) != hipSuccess ||
         hipEventCreateWithFlags(&p->ev_join, hipEventDisableTiming) != hipSuccess) {
@@ -466,8 +472,8 @@ xbar_status xbar_assemble(xbar_plan p, const double* G)
 {
     if (p == nullptr || G == nullptr) return XBAR_ERR_ARG;
     if (!set_device(p)) return XBAR_ERR_DEVICE;
-    hipLaunchKernelGGL(clear_flags_kernel, dim3(1), dim3(64), 0, p->stream, p->d.flags);
-    if (xbk_launch_reset_diag(p->d.diag, 3, p->stream) != hipSuccess) return XBAR_ERR_DEVICE;
+    hipLaunchKernelGGL(clear_state_kernel, dim3(1), dim3(64), 0, p->stream, p->d.flags, p->d.diag);
+    if (hipGetLastError() != hipSuccess) return XBAR_ERR_DEVICE;
     p->backerr_valid = false;
     if (p->timing && !p->t_condense.begin(p->stream)) return XBAR_ERR_DEVICE;
     if (p->rev) {
