@@ -8,11 +8,11 @@
 // rest of the 64-wide block is decoupled padding that no product reads).
 //
 // Bound: the dependent chain.  A row is three LT x LT x LT tile products back to back
-// on one CU's matrix cores (LT = 4: 3 x 4096 cycles, 5.1 us at the CU's float64 rate)
-// plus an LDS round trip and a barrier each; the next row's E block is requested a
+// on one CU's matrix cores (LT = 4: 4096 cycles for Q and 3072 each for Y and X'', which
+// are formed on and above the diagonal: 4.3 us at the CU's float64 rate) plus an LDS round trip and a barrier each; the next row's E block is requested a
 // row ahead, and the tolerance is a ballot per wave instead of a reduction of the
-// largest entry.  Measured: 6.7 us a row at 50 columns, 1.9 us at 32, about 1 us at 16,
-// both chains at once (32 x 700 as its reciprocal: 0.70 ms for the factor, against
+// largest entry.  Measured: 6.1 us a row at 50 columns (6.7 with whole products), 1.9 us
+// at 32, about 1 us at 16, both chains at once (32 x 700 as its reciprocal: 0.70 ms for the factor, against
 // 5.7 ms).  The slot schedule was bound by its launches instead, about 2.8 us of host
 // time each, six per pair of rows at any size.
 #include "common.h"
@@ -65,6 +65,30 @@ __device__ __forceinline__ typename Frag<T>::acc_t tile_product(const T* A, cons
     return acc;
 }
 
+// What tile_put(t, l, v) would store, transposed.
+template <typename T>
+__device__ __forceinline__ void tile_put_across(T* t, int l, typename CV4<T>::type v)
+{
+#pragma unroll
+    for (int k = 0; k < 4; ++k) t[frg<T>(Frag<T>::kidx(l >> 4, k), l & 15, 16)] = v[k];
+}
+
+// Tile of wave w: the tiles on and above the diagonal first, so that their waves are
+// spread evenly over the SIMDs (wave w on SIMD w % 4).
+template <int LT>
+__device__ __forceinline__ void chain_tile(int w, int& tr, int& tc)
+{
+    for (tr = 0; tr < LT; ++tr) {
+        if (w < LT - tr) {
+            tc = tr + w;
+            return;
+        }
+        w -= LT - tr;
+    }
+    for (tr = 1; w >= tr; ++tr) w -= tr;
+    tc = w;
+}
+
 // Chains first, first + 1, ... (one per workgroup): 0 the top chain (rows 0..kt-1),
 // 1 the bottom chain (rows m-1..kt+1), 2 the twist row, whose launch follows the
 // chains' and, with `report` set, turns a missed tolerance into kErrConv.
@@ -74,13 +98,18 @@ __global__ __launch_bounds__(64 * LT * LT) void ns_chain_kernel(NSArgs a, int fi
     constexpr int NW = LT * LT, SZ = LT * LT * 256;
     constexpr bool rounds = sizeof(T) == 8;       // third-order rounds; float32: single steps
     constexpr double done = rounds ? 6.4e-5 / 64.0 : 1e-4;
+    // Y and X'' are symmetric: their products on and above the diagonal only, where that
+    // saves a SIMD a tile (LT >= 3: 2 of 3, 3 of 4)
+    constexpr bool triangle = rounds && LT >= 3;
     using v4 = typename CV4<T>::type;
     __shared__ __align__(16) T sP[SZ], sQ[SZ], sX[2][SZ];
     __shared__ double rdg[2][16 * LT];       // reciprocals of the pivot block's diagonal
     __shared__ int pass[NW];
     const int l = threadIdx.x & 63, q = l >> 4;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int tr = w / LT, tc = w % LT, own = w * 256;
+    int tr, tc;
+    chain_tile<LT>(w, tr, tc);
+    const int own = (tr * LT + tc) * 256, across = (tc * LT + tr) * 256;
     const int n = a.n, m = a.m, kt = m / 2, chain = first + (int)blockIdx.x;
     const int rows = chain == 0 ? kt : chain == 1 ? m - 1 - kt : 1;
     if (rows <= 0) return;
@@ -143,7 +172,24 @@ __global__ __launch_bounds__(64 * LT * LT) void ns_chain_kernel(NSArgs a, int fi
             lds_barrier();
             const bool fin = __ballot(l >= NW || pass[l] != 0) == ~0ull;
             const bool last = it + (rounds ? 2 : 1) >= maxit;
-            if constexpr (rounds) {
+            if constexpr (triangle) {
+                // Y = Q X, then X'' = X + Y + Q Y (into X's buffer below the diagonal)
+                v4 y{0, 0, 0, 0};
+                if (tr <= tc) {
+                    y = tile_product<T, LT>(sQ, sX[0], tr, tc, l);
+                    tile_put<T>(sX[1] + own, l, y);
+                    if (tr < tc) tile_put_across<T>(sX[1] + across, l, y);
+                }
+                lds_barrier();
+                if (tr <= tc) {
+                    const v4 z = tile_product<T, LT>(sQ, sX[1], tr, tc, l);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) h[v] = (x[v] + y[v]) + z[v];
+                    if (tr < tc) tile_put_across<T>(sX[0] + across, l, h);
+                }
+                lds_barrier();
+                if (tr > tc) h = tile_get<T>(sX[0] + own, l);
+            } else if constexpr (rounds) {
                 // Y = Q X, then X'' = X + Y + Q Y
                 const v4 y = tile_product<T, LT>(sQ, sX[0], tr, tc, l);
                 tile_put<T>(sX[1] + own, l, y);
