@@ -1,7 +1,8 @@
 // Forward and back substitution of a plan's batch where the slab sweep (sweep.hip: one
 // workgroup walks all the row blocks for 16 input vectors) leaves the GPU waiting:
 //
-//  * sweep_small_kernel, n <= 64: both chains of the twisted order in one workgroup.
+//  * sweep_small_kernel, n <= 64: both chains of the twisted order in one workgroup, or
+//    a workgroup each.
 //    A row block is at most 4 x 4 tiles, so a step is a short dependent chain (LDS
 //    read, 4 LT matrix instructions, LDS write, barrier); the chains' steps run side by
 //    side and nothing is computed past the last live 16 x 16 tile.
@@ -82,18 +83,27 @@ __device__ __forceinline__ float fma_t(float a, float b, float c) { return __bui
 // an LDS write, a barrier and an LDS read, and at LT = 4 the 64 KB of H that a step
 // brings through one CU's L1.  Measured: 0.64 us a step at 32 columns (700 rows, 16
 // vectors: 448 us; the slab sweep 3932 us, whose one matrix-core wave walks both chains
-// in turn on padded blocks), 2.0 us at 50 columns (65 rows, 20 vectors: 132 us), 10 us
-// for 16 x 16 (99 us).
+// in turn on padded blocks), 10 us for 16 x 16 (99 us); at 50 columns 1.0 us with a
+// workgroup per chain (1.7 with both in one).
 template <int V> struct Slot { static constexpr int value = V; };
 
-template <int LT, bool UP>
-__global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
+//
+// PART: kBoth, or for more than 32 columns a workgroup per chain (blockIdx.y) and two
+// launches, kForward and kTwistBack, with the chains' last forward results handed over in
+// a.ysteps ([slab][chain], since a back chain overwrites its own in Z): half of H per
+// CU.
+enum : int { kBoth, kForward, kTwistBack };
+
+template <int LT, bool UP, int PART>
+__global__ __launch_bounds__((PART == kBoth ? 128 : 64) * LT) void sweep_small_kernel(SweepArgs a)
 {
     constexpr int n_p = 64, ldy = 16 * LT + 4, D = 4;
-    __shared__ __align__(16) double pan[2][2][16 * ldy];       // [chain][buffer][vector][CPR position]
+    __shared__ __align__(16) double pan[PART == kBoth ? 2 : 1][2][16 * ldy];   // [chain][buffer][vector][CPR position]
     const int l = threadIdx.x & 63, q = l >> 4, col = l & 15;
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const int c = w / LT, t = w % LT;
+    // without the upward back chain the second launch is the bottom chain's alone
+    const int c = PART == kBoth ? w / LT : PART == kTwistBack && !UP ? 1 : (int)blockIdx.y, t = w % LT;
+    const int pc = PART == kBoth ? c : 0;                      // the chain's panels in LDS
     const int n = a.n, m = a.m, kt = m / 2, F = kt, late = kt - (m - 1 - kt);
     const int last = F + (UP ? kt : m - 1 - kt), late_back = UP ? late : 0;
     const int slab = blockIdx.x, b = 16 * slab + col;
@@ -108,6 +118,7 @@ __global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
     const double* const Vb = a.V + (src ? (int64_t)b * m : 0);
     const int64_t blk = n_p * n_p, zrow = 16 * n_p;
     const int at = col * ldy + 16 * t + 4 * q;                 // this lane's rows in a panel
+    double* const hand = reinterpret_cast<double*>(a.ysteps) + (int64_t)slab * 2 * zrow + t * 256;
 
     auto row_of = [&](int p) {
         p = min(p, last);
@@ -166,44 +177,48 @@ __global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
         vq[D - 1] = v0;
     };
 
+    const int first = PART == kTwistBack ? F : 0;
 #pragma unroll
     for (int d = 0; d < D; ++d) {
-        load_rhs(d, rq[d], vq[d]);
-        load_h(d, ring[d]);
-    }
-    // the first row's right-hand side: the first panel, or, for a chain that starts late,
-    // what step 0 adds to its zero product
-    d4_t f0 = rhs(rq[0], vq[0]);
-    if (a.term && c == 1) {
-        const double* Vt = a.V + (int64_t)(bval ? b : 0) * n + (n - 1);
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const int k = 16 * t + Frag<double>::drow(q, v);
-            const double x = Vt[-min(k, n - 1)];
-            f0[v] = (bval && k < n) ? a.g_sense * x : 0.0;
-        }
+        load_rhs(first + d, rq[d], vq[d]);
+        load_h(first + d, ring[d]);
     }
     const bool idle = c == 1 && late == 1;
-    store4(&pan[c][0][at], idle ? d4_t{0.0, 0.0, 0.0, 0.0} : f0);
     int cur = 0;
-    lds_barrier();
+    d4_t f0{0.0, 0.0, 0.0, 0.0};
+    if constexpr (PART != kTwistBack) {
+        // the first row's right-hand side: the first panel, or, for a chain that starts late,
+        // what step 0 adds to its zero product
+        f0 = rhs(rq[0], vq[0]);
+        if (a.term && c == 1) {
+            const double* Vt = a.V + (int64_t)(bval ? b : 0) * n + (n - 1);
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int k = 16 * t + Frag<double>::drow(q, v);
+                const double x = Vt[-min(k, n - 1)];
+                f0[v] = (bval && k < n) ? a.g_sense * x : 0.0;
+            }
+        }
+        store4(&pan[pc][0][at], idle ? d4_t{0.0, 0.0, 0.0, 0.0} : f0);
+        lds_barrier();
+    }
 
     // forward, step p in ring slot d
     auto forward = [&](int p, auto slot) {
         constexpr int d = decltype(slot)::value;
-        const d4_t z = product(ring[d], pan[c][cur]);
+        const d4_t z = product(ring[d], pan[pc][cur]);
         frag_store(Z + row_of(p) * zrow, l, z);
         d4_t f = rhs(rq[(d + 1) % D], vq[(d + 1) % D]);
         if (p == 0 && idle) f = f0;
         // the next row's panel, or the forward result itself for the twist
         const d4_t y = axpy(z, f);
-        store4(&pan[c][cur ^ 1][at], p + 1 < F ? y : z);
+        store4(&pan[pc][cur ^ 1][at], p + 1 < F ? y : z);
         load_h(p + D, ring[d]);
         load_rhs(p + D, rq[d], vq[d]);
         cur ^= 1;
         lds_barrier();
     };
-    int p = 0;
+    int p = first;
     for (; p + D <= F; p += D) {
         forward(p, Slot<0>{});
         forward(p + 1, Slot<1>{});
@@ -214,23 +229,35 @@ __global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
         forward(p, Slot<0>{});
         rotate();
     }
+    if constexpr (PART == kForward) {
+        frag_store(hand + c * zrow, l, load4(&pan[pc][cur][at]));   // this lane's own entries
+        return;
+    }
     // twist row
     const d4_t ft = rhs(rq[0], vq[0]);
 #pragma unroll
     for (int d = 0; d < D; ++d) load_z(F + max(d, 1), rq[d]);
-    const d4_t yt = axpy(load4(&pan[1][cur][at]), axpy(load4(&pan[0][cur][at]), ft));
-    store4(&pan[c][cur ^ 1][at], yt);
+    d4_t zt, zb;
+    if constexpr (PART == kTwistBack) {
+        zt = frag_load<double>(hand, l);
+        zb = frag_load<double>(hand + zrow, l);
+    } else {
+        zt = load4(&pan[0][cur][at]);
+        zb = load4(&pan[1][cur][at]);
+    }
+    const d4_t yt = axpy(zb, axpy(zt, ft));
+    store4(&pan[pc][cur ^ 1][at], yt);
     cur ^= 1;
     lds_barrier();
-    const d4_t ut = product(ring[0], pan[c][cur]);
+    const d4_t ut = product(ring[0], pan[pc][cur]);
     if (UP && c == 0) frag_store(Z + kt * zrow, l, ut);
-    store4(&pan[c][cur ^ 1][at], ut);
+    store4(&pan[pc][cur ^ 1][at], ut);
     load_h(F + D, ring[0]);
     load_z(F + D, rq[0]);
     cur ^= 1;
     lds_barrier();
     rotate();
-    if (!UP && c == 0) {
+    if (PART == kBoth && !UP && c == 0) {
         for (p = F + 1; p <= last; ++p) lds_barrier();
         return;
     }
@@ -238,12 +265,12 @@ __global__ __launch_bounds__(128 * LT) void sweep_small_kernel(SweepArgs a)
     d4_t u = ut;
     auto back = [&](int p, auto slot) {
         constexpr int d = decltype(slot)::value;
-        u = axpy(product(ring[d], pan[c][cur]), rq[d]);
+        u = axpy(product(ring[d], pan[pc][cur]), rq[d]);
         if (UP) {
             if (idle && p == F + 1) u = ut;
             frag_store(Z + row_of(p) * zrow, l, u);
         }
-        store4(&pan[c][cur ^ 1][at], u);
+        store4(&pan[pc][cur ^ 1][at], u);
         load_h(p + D, ring[d]);
         load_z(p + D, rq[d]);
         cur ^= 1;
@@ -620,14 +647,31 @@ hipError_t run_steps(const SweepArgs& a, hipStream_t s)
     return hipSuccess;
 }
 
+// A workgroup per chain pays where a step is bound by its loads and the chains are longer
+// than a launch: microseconds a batch with node voltages, chain per workgroup / both in
+// one: 64 x 64 83 / 127, with 2048 vectors 126 / 170; 300 x 48 232 / 327; 3 x 40 25 / 24.
+// At 32 columns the chains gain 0.04 us a step (700 rows 385 / 413, 64 rows 56 / 56, 89 / 85
+// with 2048 vectors; 3 rows 24 / 22), and keep one workgroup.
+constexpr int kSplitRows = 8;
+
+template <int LT, bool UP>
+hipError_t run_small_up(const SweepArgs& a, hipStream_t s)
+{
+    if (LT > 2 && a.m >= kSplitRows) {
+        hipLaunchKernelGGL((sweep_small_kernel<LT, UP, kForward>), dim3(a.nslab, 2), dim3(64 * LT), 0, s, a);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((sweep_small_kernel<LT, UP, kTwistBack>), dim3(a.nslab, UP ? 2 : 1), dim3(64 * LT), 0, s, a);
+    } else {
+        hipLaunchKernelGGL((sweep_small_kernel<LT, UP, kBoth>), dim3(a.nslab), dim3(128 * LT), 0, s, a);
+    }
+    return hipGetLastError();
+}
+
 template <int LT>
 hipError_t launch_small(const SweepArgs& a, hipStream_t s)
 {
-    if (a.node_v)
-        hipLaunchKernelGGL((sweep_small_kernel<LT, true>), dim3(a.nslab), dim3(128 * LT), 0, s, a);
-    else
-        hipLaunchKernelGGL((sweep_small_kernel<LT, false>), dim3(a.nslab), dim3(128 * LT), 0, s, a);
-    return hipGetLastError();
+    return a.node_v ? run_small_up<LT, true>(a, s) : run_small_up<LT, false>(a, s);
 }
 
 // One slab a wave up to a wave per SIMD, two (on each H tile it loads) past that: with

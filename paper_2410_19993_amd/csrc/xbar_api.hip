@@ -30,7 +30,8 @@ struct Buffers {
     double* Iout = nullptr;   // [max_batch][n]
     int* flags = nullptr;     // [kNumFlags]
     unsigned long long* diag = nullptr;   // [kNumDiag]: smallest pivot key, largest backward error bits
-    void* ysteps = nullptr;   // [2 chains][2][slabs][16][n_p]: panels of the step path
+    void* ysteps = nullptr;   // [2 chains][2][slabs][16][n_p]: panels of the step path, or for
+                              // 33 to 64 columns [slabs][2 chains][16][n_p], the small sweep's
     double* sink = nullptr;   // [128]: target of the sweep's L2-pull keep-alive store
     // Newton-Schulz factor: per chain S, X[2], Q ([n_p][n_p]) and dprev ([2][n_p])
     void* ns_S[2] = {nullptr, nullptr};
@@ -418,6 +419,7 @@ xbar_status xbar_create_ordered(const xbar_geometry* geom, xbar_precision prec, 
     }
     A((void**)&d.ns_part, 2 * (n_p / 32) * (n_p / 32) * 8);
     A((void**)&d.ns_state, 6 * sizeof(xbk::NSState));
+    if (n > 32 && n <= 64 && prec == XBAR_FP64) A(&d.ysteps, 2 * (int64_t)p->nslab_max * 16 * n_p * es);
     if (xbk_step_slabs(p->n_p, p->fp32()) > 0)
         A(&d.ysteps, 4 * (int64_t)std::min(p->nslab_max, xbk_step_slabs(p->n_p, p->fp32())) * 16 * n_p * es);
     if (!transfer_by_recurrence(p)) A((void**)&d.Vunit, (int64_t)p->tr_rows * og.m * 8);
