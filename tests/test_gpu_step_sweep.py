@@ -91,3 +91,49 @@ def test_transfer_by_either_route(m, n):
             st, info = p.info()
         assert st == 0 and info.max_backward_err == before
         assert rel_err(T, ref).max() <= TOL_FP64
+
+
+@pytest.mark.parametrize("precision", ["fp64", "fp32_ir"])
+@pytest.mark.parametrize("m,n", [(20, 50), (12, 30), (9, 200)])
+def test_captured_pass_replays_the_eager_bits(m, n, precision):
+    """Assembly, factor, solve, currents and transfer of the small-block and step paths in
+    one graph: every replay, with eager work between, gives the eager bits."""
+    import torch
+
+    import paper_2410_19993_amd as xb
+    wl = workloads.random_crossbar(m, n, 18, 8600 + n, r_wl=2.5, r_bl=2.5)
+    G, V = torch.from_numpy(wl.G).cuda(), torch.from_numpy(np.ascontiguousarray(wl.V)).cuda()
+    nv = torch.empty((18, 2 * m * n), dtype=torch.float64, device="cuda")
+    I = torch.empty((18, n), dtype=torch.float64, device="cuda")
+    T = torch.empty((m, n), dtype=torch.float64, device="cuda")
+    s = torch.cuda.Stream()
+    log(f"case capture {m}x{n} {precision}")
+    with xb.Plan(m, n, 2.5, 2.5, 50.0, 50.0, precision, max_batch=32, stream=s, ordering="rows") as p:
+        def step():
+            p.assemble(G)
+            p.factor()
+            p.solve_batch(V, nv)
+            p.currents(I)
+            p.transfer(T)
+        with torch.cuda.stream(s):
+            step()
+        s.synchronize()
+        eager = [x.clone() for x in (I, nv, T)]
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=s):
+            step()
+        for _ in range(3):
+            for x in (I, nv, T):
+                x.fill_(-1.0)
+            torch.cuda.synchronize()
+            graph.replay()
+            torch.cuda.synchronize()
+            assert all(torch.equal(x, e) for x, e in zip((I, nv, T), eager))
+            with torch.cuda.stream(s):
+                p.assemble(G * 1.01)
+                p.factor()
+            s.synchronize()
+        st, _ = p.info()
+    assert st == 0
+    assert rel_err(eager[0].cpu().numpy(), oracle.solve_workload(wl).currents).max() <= (
+        TOL_FP64 if precision == "fp64" else TOL_IR)
