@@ -23,7 +23,10 @@
 //    for its inverse, and on the diagonal by the change of 1 / S_jj.  A round is the last
 //    once every |Q| entry is <= 2.5e-7 (||I - X S|| <= 4.1e-15): one round a row for
 //    devices of 1 to 100 uS on 1.5 ohm wires, two for devices of 2 mS and in the last
-//    row.  The first row, and a row whose rounds miss the tolerance, is eliminated;
+//    row.  The first row, and a row whose rounds miss the tolerance, is eliminated, and so
+//    is every row from conductances so large that rounding may cost S_i its definiteness
+//    (round_limit): the rounds find the inverse of an indefinite block as readily as any,
+//    while an elimination meets its pivots;
 //  * the product H_i Y runs on the matrix cores too: a wave owns every eighth (fourth)
 //    group of 16 input vectors, and keeps their forward results in the accumulator
 //    layout (item v of lane l = 16 q + c is row q + 4v of a 16-row tile, vector c of a
@@ -70,6 +73,7 @@ struct TileArgs {
     int m, n, B, Bp;
     int unit;           // 1: input vector b is the unit vector e_b (V is not read)
     double g_wl, g_bl, g_src, g_sense;
+    double g_rounds;    // rows are inverted by rounds up to this conductance (round_limit)
     const double* G;    // [T][m][n]
     const double* V;    // [T][B][m]
     double* I;          // [T][B][n]
@@ -77,6 +81,20 @@ struct TileArgs {
 
 constexpr double kBlockNsDone = 2.5e-7;  // largest |Q| entry of a row's last round
 constexpr int kBlockRounds = 3;          // rounds before a row is eliminated: ||Q|| <= 1/4 cubes to 4e-6 in two
+
+// Largest conductance for which S_i, as computed, is strictly diagonally dominant with a
+// positive diagonal, so that its pivots are positive; rows past it are eliminated, which
+// checks them.  Without rounding S_i 1 >= below, the conductance under the row: the word
+// line's term G - G T^-1 G 1 is not negative, and g_bl H_{i-1} 1 <= 1.  Rounding changes
+// the row sums by at most 2e-12 G (products of up to 64 ratios, 3e-14 each) and
+// 1e-14 (2 G + 4 g_bl) (H_{i-1}, whose condition is at most (2 G + 4 g_bl) / g_bl): a tenth
+// of `below` where G + g_bl <= 1e10 below.  The elimination also takes pivots past 1e300
+// for bad.
+double round_limit(double g_bl, double g_sense)
+{
+    if (!(g_bl <= 1e299 && g_sense <= 1e299)) return -1.0;
+    return std::fmin(1e10 * std::fmin(g_bl, g_sense) - g_bl, 1e299);
+}
 
 __device__ __forceinline__ double nanmax(double a, double b)
 {
@@ -191,19 +209,95 @@ __device__ __attribute__((noinline)) bool eliminate(lds_double* T, lds_double* w
     return good;
 }
 
+constexpr int kChainRows = 32;           // rows whose word-line chains are walked together
+
+// Per row: conductances, r_j, the diagonal of T^-1, and by segments of eight columns the
+// products of the r before a column of the segment and of all of them.
+template <int NP>
+struct Chains {
+    double g[kChainRows][NP + 1], r[kChainRows][NP + 1], d[kChainRows][NP + 1];
+    double pre[kChainRows][NP], seg[kChainRows][NP / 8];
+};
+template <int NP> using lds_chains = __attribute__((address_space(3))) Chains<NP>;
+typedef __attribute__((address_space(3))) int lds_int;
+
+// The word-line chains of `rows` rows, a lane per row (excess form, no subtraction):
+//   e_0 = G_0 + g_src, e_j = G_j + g_wl e_{j-1} / p_{j-1}, p_j = e_j + g_wl [j < n-1];
+// then r_j = g_wl / p_j and, from the far end, the diagonal of T^-1:
+//   d_k = (1 + g_wl r_k d_{k+1}) / p_k.
+// Eight columns of a row pass through registers at a time: column by column, a lane waits
+// for what it has just stored (5000 crossbars of 8 x 8 318 us, 310 so).  *beyond becomes
+// infinite at a conductance past g_rounds.  A function of its own, like eliminate: inlined,
+// 1024 crossbars of 64 x 64 with 256 vectors took 5.82 ms, 5.54 so.  Ends with a barrier.
+template <int NP>
+__device__ __attribute__((noinline)) void walk_chains(lds_chains<NP>* c, lds_int* bad, lds_double* beyond,
+                                                      const double* __restrict__ G, int rows, int n, double gw,
+                                                      double g_src, double g_rounds)
+{
+    const int tid = threadIdx.x;
+    for (int e = tid; e < rows * n; e += 64 * tile_waves<NP>) {
+        const double g = G[e];
+        c->g[e / n][e % n] = g;
+        if (!(g > 0.0 && g <= 1e300)) *bad = 1;
+        if (!(g <= g_rounds)) *beyond = HUGE_VAL;
+    }
+    lds_barrier();
+    if (tid < rows) {
+        lds_double *gr = c->g[tid], *rp = c->r[tid], *d = c->d[tid];
+        double e = gr[0] + g_src;
+        double rc = recip(e + (n > 1 ? gw : 0.0));
+        d[0] = rc;
+        for (int j0 = 0; j0 < n; j0 += 8) {
+            double g[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) g[u] = gr[j0 + u];        // columns past n: unused
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int j = j0 + u;
+                if (j == 0 || j >= n) continue;
+                e = g[u] + gw * e * rc;
+                rc = recip(e + (j < n - 1 ? gw : 0.0));
+                d[j] = rc;
+            }
+        }
+        double x = rc;
+        for (int k0 = (n - 1) & ~7; k0 >= 0; k0 -= 8) {
+            double p[8], r[8], f = 1.0;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = d[k0 + u];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                r[u] = gw * p[u];
+                if (k0 + u < n) c->pre[tid][k0 + u] = f;
+                f *= r[u];
+            }
+            if (k0 + 7 < n - 1) c->seg[tid][k0 >> 3] = f;
+#pragma unroll
+            for (int u = 7; u >= 0; --u) {
+                const int k = k0 + u;
+                if (k >= n - 1) continue;
+                rp[k] = r[u];
+                x = p[u] * fma(gw * r[u], x, 1.0);
+                d[k] = x;
+            }
+        }
+    }
+    lds_barrier();
+}
+
 template <int NP>
 __global__ __launch_bounds__(64 * tile_waves<NP>) void tile_currents_kernel(TileArgs a)
 {
     constexpr int LD = NP + 2;                         // row stride of the LDS blocks
-    constexpr int W = tile_waves<NP>, threads = 64 * W;
+    constexpr int W = tile_waves<NP>;
     constexpr int NT = NP / 16;                        // 16-row tiles of the product
     constexpr int NG = 16 / W;                         // groups of 16 vectors of a wave
     constexpr int CT = NP == 64 ? 2 : 1;               // tiles of a round that a wave owns
-    constexpr int R = 32;                              // rows whose chains are walked together
+    constexpr int R = kChainRows;
     __shared__ __align__(16) double blk[2][NP * LD];
-    __shared__ __align__(16) double gs[R][NP + 1], rs[R][NP + 1], ds[R][NP + 1];
-    __shared__ double pre[R][NP], seg[R][NP / 8];
+    __shared__ __align__(16) Chains<NP> chains;
     __shared__ double cr[NP], rdiag[2][NP], wmx[W];
+    __shared__ double beyond;                          // 0, or infinite from a conductance past g_rounds on
     __shared__ int bad;
 
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
@@ -216,7 +310,10 @@ __global__ __launch_bounds__(64 * tile_waves<NP>) void tile_currents_kernel(Tile
     const double* V = a.V + (t * a.B + b0) * m;
     double* I = a.I + (t * a.B + b0) * n;
     const double gw = a.g_wl, gb = a.g_bl;
-    if (tid == 0) bad = 0;
+    if (tid == 0) {
+        bad = 0;
+        beyond = 0.0;
+    }
     lds_barrier();
     // the wave's tiles of S_i and H_i: row tile wr, column tiles wc .. wc + CT - 1
     const int wr = NP == 64 ? w >> 1 : NP == 32 ? (w & 3) >> 1 : 0, wc = NP > 16 ? CT * (w & 1) : 0;
@@ -280,61 +377,20 @@ __global__ __launch_bounds__(64 * tile_waves<NP>) void tile_currents_kernel(Tile
             const int b = 16 * (W * g + w) + l16;
             vi[g] = (b < B) ? (a.unit ? (b0 + b == i ? 1.0 : 0.0) : V[(int64_t)b * m + i]) : 0.0;
         }
-        if (ir == 0) {
-            // ---- the word-line chains of the next R rows, a lane per row (excess form, no
-            // subtraction): e_0 = G_0 + g_src, e_j = G_j + g_wl e_{j-1} / p_{j-1},
-            // p_j = e_j + g_wl [j < n-1]; then r_j = g_wl / p_j and, from the far end, the
-            // diagonal of T^-1: d_k = (1 + g_wl r_k d_{k+1}) / p_k.  pre: the product of the r
-            // of k's segment of eight before k; seg: that of the whole segment.
-            const int rows = min(R, m - i);
-            for (int e = tid; e < rows * n; e += threads) {
-                const double g = G[(int64_t)i * n + e];
-                gs[e / n][e % n] = g;
-                if (!(g > 0.0 && g <= 1e300)) bad = 1;
-            }
-            lds_barrier();
-            if (tid < rows) {
-                const double *gr = gs[tid];
-                double *rp = rs[tid], *d = ds[tid];
-                double e = gr[0] + a.g_src;
-                double rc = recip(e + (n > 1 ? gw : 0.0));
-                d[0] = rc;
-                for (int j = 1; j < n; ++j) {
-                    e = gr[j] + gw * e * rc;
-                    rc = recip(e + (j < n - 1 ? gw : 0.0));
-                    d[j] = rc;
-                }
-                double x = rc;
-                for (int k = n - 2; k >= 0; --k) {
-                    const double pk = d[k], rk = gw * pk;
-                    rp[k] = rk;
-                    x = pk * fma(gw * rk, x, 1.0);
-                    d[k] = x;
-                }
-                double f = 1.0;
-                for (int k = 0; k < n - 1; ++k) {
-                    pre[tid][k] = f;
-                    f *= rp[k];
-                    if ((k & 7) == 7) {
-                        seg[tid][k >> 3] = f;
-                        f = 1.0;
-                    }
-                }
-                pre[tid][n - 1] = f;
-            }
-            lds_barrier();
-        }
-        const double* gr = gs[ir];
+        if (ir == 0)
+            walk_chains<NP>((lds_chains<NP>*)&chains, (lds_int*)&bad, (lds_double*)&beyond, G + (int64_t)i * n,
+                            min(R, m - i), n, gw, a.g_src, a.g_rounds);
+        const double* gr = chains.g[ir];
         // ---- T_i^-1[j][k] = r_j ... r_{k-1} d_k = T_i^-1[k][j], j <= k: wave w stores the rows of
         // segment w, lane k those of column k
         if (w < NP / 8 && lane < n && 8 * w <= lane) {
-            const double* rp = rs[ir];
+            const double* rp = chains.r[ir];
             const int k = lane, sk = k >> 3;
-            double x = ds[ir][k] * (w < sk ? pre[ir][k] : 1.0), f[8], y[NP / 8];
+            double x = chains.d[ir][k] * (w < sk ? chains.pre[ir][k] : 1.0), f[8], y[NP / 8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) f[u] = rp[8 * w + u];
 #pragma unroll
-            for (int u = 1; u < NP / 8; ++u) y[u] = seg[ir][u];
+            for (int u = 1; u < NP / 8; ++u) y[u] = chains.seg[ir][u];
 #pragma unroll
             for (int u = 1; u < NP / 8; ++u) x *= u > w && u < sk ? y[u] : 1.0;
 #pragma unroll
@@ -404,11 +460,12 @@ __global__ __launch_bounds__(64 * tile_waves<NP>) void tile_currents_kernel(Tile
             put(Hp, x);
             for (int round = 0; round < kBlockRounds; ++round) {
                 lds_barrier();
+                const double past = beyond;            // infinite: no round is the last
                 dv4 qv[CT], y[CT];
 #pragma unroll
                 for (int C = 0; C < CT; ++C) qv[C] = y[C] = dv4{0.0, 0.0, 0.0, 0.0};
                 product(qv, Hp, Tb);                   // X_0 S
-                double mx = 0.0;
+                double mx = past;
 #pragma unroll
                 for (int C = 0; C < CT; ++C)
 #pragma unroll
@@ -504,7 +561,7 @@ hipError_t xbk_launch_tile_currents(int T, int m, int n, int B, double g_wl, dou
     if ((block != 16 && block != 32 && block != 64) || block < n || split < 1 || split > 4) return hipErrorInvalidValue;
     const int Bp = (B + split - 1) / split;
     const int parts = (B + Bp - 1) / Bp;
-    TileArgs a{m, n, B, Bp, unit ? 1 : 0, g_wl, g_bl, g_src, g_sense, G, V, I};
+    TileArgs a{m, n, B, Bp, unit ? 1 : 0, g_wl, g_bl, g_src, g_sense, round_limit(g_bl, g_sense), G, V, I};
     const dim3 grid((unsigned)T, (unsigned)parts);
     if (block == 16)
         hipLaunchKernelGGL(tile_currents_kernel<16>, grid, dim3(64 * tile_waves<16>), 0, s, a);

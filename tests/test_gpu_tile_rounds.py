@@ -63,3 +63,27 @@ def test_column_and_tile_workgroups_give_the_same_bits(count, m, n):
     for t in (0, 7, 8, count - 1):
         assert np.array_equal(run(G[t:t + 1].contiguous(), V[t:t + 1].contiguous())[0], out[t])
     assert rel_err(out[1], oracle.solve(G[1].cpu().numpy(), V[1].cpu().numpy(), *r).currents).max() <= TOL_FP64
+
+
+@pytest.mark.parametrize("n", [1, 8, 16, 17, 32, 33, 64])
+def test_rounds_keep_the_pivot_check(n):
+    """A row block whose pivots are not positive gives NaN currents also in rows after the
+    first.  Devices of 2^60 S swallow the wire conductances: with r_wl = 10 kohm,
+    S_1 = -g_bl^2 H_0 - (couplings of 1e-4 S) exactly, a negative diagonal of -1/3 S, whose
+    inverse Newton-Schulz rounds find as readily as that of a positive block.  A negative
+    pivot would make a current of positive inputs negative.  The other crossbars of the
+    call are unaffected."""
+    import torch
+
+    import paper_2410_19993_amd as xb
+    log(f"case pivot sign n={n}")
+    rng = np.random.default_rng(n)
+    m, B, r = 4, 3, (1e4, 3.0, 40.0, 60.0)
+    G = np.exp(rng.uniform(np.log(1e-6), np.log(1e-4), (5, m, n)))
+    G[1, 1], G[2, 2], G[3, 3] = 2.0 ** 60, 2.0 ** 60, 2.0 ** 60
+    V = rng.uniform(0.1, 0.5, (5, B, m))
+    I = xb.tiles_currents(torch.from_numpy(G).cuda(), torch.from_numpy(V).cuda(), *r).cpu().numpy()
+    for t in (0, 4):
+        assert rel_err(I[t], oracle.solve(G[t], V[t], *r).currents).max() <= TOL_FP64
+    for t in (1, 2, 3):
+        assert np.isnan(I[t]).all(), t
