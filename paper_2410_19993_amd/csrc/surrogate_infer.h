@@ -17,7 +17,7 @@ extern "C" {
  * rows may differ in rounding.  2 <= depth <= 5, 1 <= C <= XBAR_SG_MAX_CHANNELS, m, n <=
  * XBAR_SG_MAX_LINE.  work: 16-byte aligned device memory of at least
  * xbar_sg_infer_workspace_bytes bytes (-1: a size this call does not take), overlapping
- * nothing else.  est may be NULL. */
+ * nothing else.  I must not overlap G or V; est (NULL: none) must not overlap I. */
 int64_t xbar_sg_infer_workspace_bytes(int32_t B, int32_t m, int32_t n, int32_t C, int32_t depth);
 xbar_status xbar_sg_infer_bf16(int32_t B, int32_t m, int32_t n, int32_t C, int32_t depth, const double* G,
                                const double* V, const double* r, const float* params, void* work,

@@ -444,9 +444,11 @@ xbar_status xbar_sg_infer_bf16(int32_t B, int32_t m, int32_t n, int32_t C, int32
     const int64_t sizes[4] = {(int64_t)B * m * n * 8, (int64_t)B * m * 8, (int64_t)B * 8,
                               (int64_t)params_before(depth, C, depth) * 4};
     for (int k = 0; k < 4; ++k)
-        if (meets(I, ni, ins[k], sizes[k]) || (est && meets(est, ni, ins[k], sizes[k])) ||
-            meets(work, need, ins[k], sizes[k]))
-            return XBAR_ERR_ARG;
+        if (meets(work, need, ins[k], sizes[k])) return XBAR_ERR_ARG;
+    // as xbar_sg_predict: I may not lie on G or V.  (Outputs on the other inputs are sound:
+    // the last kernel alone writes them, and it reads the workspace only.)
+    for (int k = 0; k < 2; ++k)
+        if (meets(I, ni, ins[k], sizes[k])) return XBAR_ERR_ARG;
     if (meets(work, need, I, ni) || (est && (meets(work, need, est, ni) || meets(est, ni, I, ni)))) return XBAR_ERR_ARG;
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     char* w = static_cast<char*>(work);

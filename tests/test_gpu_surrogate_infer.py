@@ -49,3 +49,30 @@ def test_sizes_outside_the_one_pass_call():
     from paper_2410_19993_amd import _lib
     for args in ((1, 8, 8, 8, 6), (1, 8, 8, 33, 4), (1, 2049, 8, 8, 4), (0, 8, 8, 8, 4), (1, 8, 8, 8, 1)):
         assert _lib.xbar_sg_infer_workspace_bytes(*args) == -1
+
+
+@pytest.mark.parametrize("which", ["out_on_r", "est_on_r", "est_on_V"])
+def test_outputs_on_inputs_that_are_read_before_them(which):
+    """Outputs in the place of an input that the currents' last step does not read (the
+    resistances, or for the estimates the input vectors) are taken, and are what separate
+    buffers receive; currents on G or V are refused."""
+    import torch
+
+    from paper_2410_19993_amd import _lib
+    from paper_2410_19993_amd.surrogate import Surrogate
+    rng = np.random.default_rng(7)
+    B, m, n = (5, 33, 33) if which == "est_on_V" else (5, 33, 1)
+    log(f"case infer {which}")
+    G = torch.from_numpy(np.exp(rng.uniform(np.log(1e-6), np.log(1e-4), (B, m, n)))).cuda()
+    V = torch.from_numpy(rng.uniform(0.0, 0.5, (B, m))).cuda()
+    r = torch.from_numpy(rng.uniform(1.0, 5.0, B)).cuda()
+    net = Surrogate(channels=8, seed=3, depth=3, zero_last=False)
+    e0 = torch.empty((B, n), dtype=torch.float64, device="cuda")
+    I0 = net.predict(G, V, r, est=e0)
+    out = r.view(B, 1) if which == "out_on_r" else torch.empty_like(I0)
+    est = r.view(B, 1) if which == "est_on_r" else V if which == "est_on_V" else torch.empty_like(e0)
+    I = net.predict(G, V, r, out=out, est=est)
+    assert torch.equal(I, I0) and torch.equal(est, e0)
+    G2 = G.view(-1)[:B * n].view(B, n)
+    with pytest.raises(_lib.XbarError):
+        net.predict(G, V, r, out=G2)
