@@ -872,10 +872,10 @@ xbar_status xbar_factor(xbar_plan p)
         if (launch_gj(p) != hipSuccess) return XBAR_ERR_DEVICE;
     } else {
         // AUTO reads the schedule back (and learns its launch counts) until it has
-        // counts from an earlier factorization of this plan; then it runs asynchronously
+        // counts from an earlier factorization of this plan (blocks of 64 need none); then
+        // it runs asynchronously
         const bool chains = p->n_p == 64;
-        const bool checked = chains ? p->factor_method == XBAR_FACTOR_CHECKED
-                                    : p->factor_method != XBAR_FACTOR_AUTO || !p->ns_hint_valid;
+        const bool checked = p->factor_method != XBAR_FACTOR_AUTO || (!chains && !p->ns_hint_valid);
         p->ns_async = !checked && !chains;
         bool failed = false;
         if ((chains ? run_ns_chains(p, checked, &failed) : run_ns(p, checked, &failed)) != hipSuccess)

@@ -66,3 +66,29 @@ def test_shared_launch_factor_matches_oracle(m, n, precision):
             assert rel_err(I, ref.currents).max() <= tol and node_rel_err(nv, ref.node_v).max() <= tol
             outs.append(I)
         assert np.array_equal(outs[0], outs[1])
+
+
+@pytest.mark.parametrize("method", ["ns", "checked"])
+@pytest.mark.parametrize("n", [16, 64, 65])
+def test_checked_factors_wait_for_their_outcome(n, method):
+    """Both methods synchronise the plan's stream at every block size, also behind work
+    that is still queued there."""
+    import torch
+
+    import paper_2410_19993_amd as xb
+    wl = workloads.random_crossbar(9, n, 1, 9950 + n)
+    G = torch.from_numpy(wl.G).cuda()
+    s = torch.cuda.Stream()
+    a = torch.randn((4096, 4096), dtype=torch.float64, device="cuda")
+    torch.cuda.synchronize()
+    log(f"case {method} n={n}")
+    with xb.Plan(9, n, 2.5, 2.5, 50.0, 50.0, "fp64", max_batch=1, stream=s, ordering="rows",
+                 factor_method=method) as p:
+        for _ in range(2):
+            with torch.cuda.stream(s):
+                p.assemble(G)
+                for _ in range(20):
+                    a @ a                                  # tens of milliseconds
+                p.factor()
+                assert s.query()
+        assert p.info()[0] == 0
