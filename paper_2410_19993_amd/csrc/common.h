@@ -379,9 +379,11 @@ hipError_t xbk_launch_sweep_parts(const xbk::SweepArgs& a, hipStream_t s);   // 
 // float64 sweep of a plan (one crossbar): picks the kernels by block size and batch (sweep_rows.hip)
 hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s);
 int xbk_step_slabs(int n_p, bool fp32);   // slabs up to which it runs step by step over the GPU
+int xbk_step_sweeps(int m, int n_p, int nslab, int expected);   // refinement sweeps it takes step by step, of `expected`
 hipError_t xbk_launch_recover(const xbk::RecoverArgs& a, hipStream_t s);
 hipError_t xbk_launch_sweep_ir(const xbk::SweepArgs& a, hipStream_t s);
-hipError_t xbk_launch_sweep_ir_plan(const xbk::SweepArgs& a, hipStream_t s);   // float32 counterpart of xbk_launch_sweep_plan
+// float32 counterpart of xbk_launch_sweep_plan; the first step_sweeps sweeps may go by steps
+hipError_t xbk_launch_sweep_ir_plan(const xbk::SweepArgs& a, int step_sweeps, hipStream_t s);
 hipError_t xbk_launch_residual(const xbk::ResidualArgs& a, hipStream_t s);
 int xbk_backward_error_max_n();     // widest crossbar the backward-error kernel measures
 // Krylov refinement kernels (gmres.hip); X_i = X + i P

@@ -364,7 +364,6 @@ hipError_t launch_recover_rows(const SweepArgs& a, hipStream_t s)
 // vector).  Refinement sweeps (float32, with their residual) as launches / slab per
 // workgroup: 2048 vectors 38 / 48 at 512, 1536 vectors 21 / 27 at 320, 17 / 20 at 256.
 constexpr int kStepSlabs = 64, kPartSlabs = 128;
-constexpr int kStepSweeps = 6;      // refinement sweeps taken by steps
 
 template <typename T>
 struct StepJob {
@@ -708,6 +707,25 @@ int xbk_step_slabs(int n_p, bool fp32)
     return n_p <= 128 ? 0 : fp32 ? xbk::kPartSlabs : xbk::kStepSlabs;
 }
 
+// A refinement queues every sweep that it may need.  One that finds its slabs finished is
+// one launch in the slab sweep, but m + 3 by steps, 1.8 to 3.5 us each; so by steps go the
+// sweeps expected, and past them as many as those gain, six at most (a float32 factor takes
+// 3 to 5 to the default tolerance, 2 to a loose one).  A sweep's microseconds per row, slab
+// sweep (and 0.023 a slab) against steps (and `per` a slab), measured at 256 and 512 rows
+// with 1, 32 and 128 slabs; 3 rows of 192 columns, 16 vectors to 1e-3: 122 us by slab sweeps,
+// 182 with six by steps, 136 with three.
+int xbk_step_sweeps(int m, int n_p, int nslab, int expected)
+{
+    constexpr int most = 6;
+    static constexpr double slab[] = {10.4, 13.2, 20.4, 25.0, 35.0, 41.0};     // n_p = 192 .. 512
+    static constexpr double step[] = {4.3, 5.3, 6.2, 7.0, 7.8, 9.0};
+    static constexpr double per[] = {0.063, 0.073, 0.1, 0.131, 0.181, 0.2};
+    const int k = n_p / 64 - 3;
+    if (k < 0 || k > 5) return 0;
+    const double gain = m * (slab[k] + 0.023 * nslab - step[k] - per[k] * nslab), idle = 3.5 * (m + 3);
+    return std::min(most, expected + (gain > 0.0 ? (int)(expected * gain / idle) : 0));
+}
+
 hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s)
 {
     if (a.batch > 1 || a.unit) return hipErrorInvalidValue;
@@ -737,10 +755,9 @@ hipError_t xbk_launch_sweep_plan(const xbk::SweepArgs& a, hipStream_t s)
     }
 }
 
-hipError_t xbk_launch_sweep_ir_plan(const xbk::SweepArgs& a, hipStream_t s)
+hipError_t xbk_launch_sweep_ir_plan(const xbk::SweepArgs& a, int step_sweeps, hipStream_t s)
 {
-    // past the sweeps that a slab needs, the slab sweep, whose launch ends at once
-    if (a.m < 3 || a.ysteps == nullptr || a.nslab > xbk_step_slabs(a.n_p, true) || a.iter >= xbk::kStepSweeps)
+    if (a.m < 3 || a.ysteps == nullptr || a.nslab > xbk_step_slabs(a.n_p, true) || a.iter >= step_sweeps)
         return xbk_launch_sweep_ir(a, s);
     switch (a.n_p / 64) {
         case 3: return xbk::run_ir_steps_nt<3>(a, s);

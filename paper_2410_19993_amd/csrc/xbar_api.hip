@@ -914,7 +914,7 @@ xbar_status xbar_factor(xbar_plan p)
 // twice; every launch is queued without a host read-back.
 static_assert(xbk::kGmRestart == XBAR_GMRES_RESTART, "restart length of the header");
 
-xbar_status gmres_solve(xbar_plan p, xbk::SweepArgs s, xbk::ResidualArgs r, int B)
+xbar_status gmres_solve(xbar_plan p, xbk::SweepArgs s, xbk::ResidualArgs r, int B, int steps)
 {
     Buffers& d = p->d;
     constexpr int K = xbk::kGmRestart;
@@ -937,7 +937,7 @@ xbar_status gmres_solve(xbar_plan p, xbk::SweepArgs s, xbk::ResidualArgs r, int 
         s.Uin = uin;
         s.Uout = uout;
         if (p->timing && !p->t_ir_sweep.begin(p->stream)) return false;
-        if (!ok(xbk_launch_sweep_ir_plan(s, p->stream))) return false;
+        if (!ok(xbk_launch_sweep_ir_plan(s, steps, p->stream))) return false;
         return !p->timing || p->t_ir_sweep.end(p->stream);
     };
     auto resid = [&](const double* u, double* out, int matvec) {
@@ -1027,6 +1027,9 @@ xbar_status xbar_solve_batch(xbar_plan p, const double* V, int32_t B, double* no
         // corrects U by the solution for the float64 residual of the previous U.
         hipLaunchKernelGGL(clear_slabs_kernel, dim3((16 * nslab + 255) / 256), dim3(256), 0, p->stream,
                            p->d.slab_done, p->d.dnorm, p->d.norms, nslab);
+        // sweeps taken by steps; a bfloat16 factor needs 10 to 30 to the default tolerance
+        const bool bf16 = p->prec != XBAR_FP32_IR, tight = p->ir_tol < 1e-9;
+        const int steps = xbk_step_sweeps(s.m, s.n_p, nslab, tight ? (bf16 ? 6 : 3) : (bf16 ? 3 : 2));
         s.max_iter = 1 + p->ir_max_iter;
         s.tol = p->ir_tol;
         s.R = p->d.R;
@@ -1053,7 +1056,7 @@ xbar_status xbar_solve_batch(xbar_plan p, const double* V, int32_t B, double* no
         r.term = s.term;
         r.g_sense = 1.0 / p->g.r_sense;
         if (p->prec == XBAR_BF16_GMRES_IR) {
-            const xbar_status gs = gmres_solve(p, s, r, B);
+            const xbar_status gs = gmres_solve(p, s, r, B, steps);
             if (gs != XBAR_OK) return gs;
             s.max_iter = 0;                  // the loop below is the classical refinement
         }
@@ -1068,7 +1071,7 @@ xbar_status xbar_solve_batch(xbar_plan p, const double* V, int32_t B, double* no
                 if (p->timing && !p->t_residual.end(p->stream)) return XBAR_ERR_DEVICE;
             }
             if (p->timing && !p->t_ir_sweep.begin(p->stream)) return XBAR_ERR_DEVICE;
-            if (xbk_launch_sweep_ir_plan(s, p->stream) != hipSuccess) return XBAR_ERR_DEVICE;
+            if (xbk_launch_sweep_ir_plan(s, steps, p->stream) != hipSuccess) return XBAR_ERR_DEVICE;
             if (p->timing && !p->t_ir_sweep.end(p->stream)) return XBAR_ERR_DEVICE;
         }
     }

@@ -137,3 +137,47 @@ def test_captured_pass_replays_the_eager_bits(m, n, precision):
     assert st == 0
     assert rel_err(eager[0].cpu().numpy(), oracle.solve_workload(wl).currents).max() <= (
         TOL_FP64 if precision == "fp64" else TOL_IR)
+
+
+def _graph_nodes(graph):
+    """Number of nodes of a captured torch graph."""
+    import ctypes
+    with open("/proc/self/maps") as f:
+        path = next(line.split()[-1] for line in f if "libamdhip64" in line)
+    nodes = ctypes.c_size_t(0)
+    assert ctypes.CDLL(path).hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+    return nodes.value
+
+
+@pytest.mark.parametrize("m,n,B,tol,sweeps", [(3, 192, 16, 1e-3, 3), (8, 192, 16, 1e-6, 4), (3, 192, 2048, 0.0, 3),
+                                              (64, 256, 2048, 1e-6, 2), (3, 512, 16, 0.0, 6)])
+def test_refinement_queues_few_idle_steps(m, n, B, tol, sweeps):
+    """Launches that a refinement queues: m + 3 for each of its first `sweeps` sweeps (two
+    panels formed, m / 2 forward, the twist, m / 2 back, the decision; m rounded up to even),
+    one for each later sweep, one for each residual, one to clear the slabs' state.  A short
+    chain or a loose tolerance does not queue long runs of steps that find nothing to do."""
+    import torch
+
+    import paper_2410_19993_amd as xb
+    wl = workloads.random_crossbar(m, n, B, 8650 + n, r_wl=2.5, r_bl=2.5)
+    G, V = torch.from_numpy(wl.G).cuda(), torch.from_numpy(wl.V).cuda()
+    s = torch.cuda.Stream()
+    log(f"case {wl.name} tol={tol}")
+    with xb.Plan(m, n, 2.5, 2.5, 50.0, 50.0, "fp32_ir", max_batch=B, ir_tol=tol, ir_max_iter=10, stream=s,
+                 ordering="rows") as p:
+        with torch.cuda.stream(s):
+            p.assemble(G)
+            p.factor()
+            p.solve_batch(V)
+        s.synchronize()
+        graph = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(graph, stream=s):
+            p.solve_batch(V)
+        st, info = p.info()
+        I = p.currents().cpu().numpy()
+    log(f"   {info.ir_iters} sweeps, {_graph_nodes(graph)} launches")
+    g = wl.geom
+    ref = oracle.solve(wl.G, wl.V[:2], g.r_wl, g.r_bl, g.r_src, g.r_sense).currents
+    assert st == 0 and rel_err(I[:2], ref).max() <= max(TOL_IR, 10 * tol)
+    per_sweep = 2 + 2 * (m // 2) + 1 + 1
+    assert _graph_nodes(graph) <= sweeps * per_sweep + (11 - sweeps) + 10 + 1
