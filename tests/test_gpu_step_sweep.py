@@ -181,3 +181,60 @@ def test_refinement_queues_few_idle_steps(m, n, B, tol, sweeps):
     assert st == 0 and rel_err(I[:2], ref).max() <= max(TOL_IR, 10 * tol)
     per_sweep = 2 + 2 * (m // 2) + 1 + 1
     assert _graph_nodes(graph) <= sweeps * per_sweep + (11 - sweeps) + 10 + 1
+
+
+@pytest.mark.parametrize("m,n,B", [(24, 192, 33), (16, 320, 16), (9, 448, 20)])
+def test_refinement_past_the_steps(m, n, B):
+    """A solve that is not finished when its sweeps by steps end: the slab sweep goes on from
+    their state (solution buffer, residual, last corrections) to the same bits and count as
+    when it runs alone, in a batch past the steps' limit, and to the oracle's currents.  A
+    bfloat16 factor gains about two digits a sweep."""
+    wl = workloads.random_crossbar(m, n, B, 8000 + n, r_wl=1.5, r_bl=3.0, r_src=40.0, r_sense=60.0)
+    log(f"case {wl.name} bf16_ir")
+    kw = dict(precision="bf16_ir", ordering="rows", ir_max_iter=40)
+    I, nv, (st, info) = gpu_solve(wl.G, wl.V, wl.geom, **kw)
+    log(f"   status {st}, {info.ir_iters} sweeps")
+    assert st == 0 and info.ir_iters > 6
+    ref = oracle.solve_workload(wl)
+    assert rel_err(I, ref.currents).max() <= TOL_IR and node_rel_err(nv, ref.node_v).max() <= TOL_IR
+    V = np.tile(wl.V, (-(-(16 * 128 + 1) // B), 1))
+    Ib, nvb, (stb, infob) = gpu_solve(wl.G, V, wl.geom, **kw)
+    assert stb == 0 and infob.ir_iters >= info.ir_iters    # (its slabs hold other vectors too)
+    k = B // 16 * 16
+    assert np.array_equal(Ib[:k], I[:k]) and np.array_equal(nvb[:k], nv[:k])
+
+
+@pytest.mark.parametrize("n", [192, 512])
+def test_refinement_by_steps_reports_non_convergence(n):
+    """One correction sweep cannot reach a 1e-15 estimate: the steps' decision flags it as the
+    slab sweep's does, and leaves the last solution."""
+    from paper_2410_19993_amd import _lib
+    B = 20
+    wl = workloads.random_crossbar(12, n, B, 8050 + n)
+    log(f"case {wl.name} fp32_ir, one correction")
+    kw = dict(precision="fp32_ir", ordering="rows", ir_tol=1e-15, ir_max_iter=1)
+    I, nv, (st, info) = gpu_solve(wl.G, wl.V, wl.geom, **kw)
+    assert st == _lib.XBAR_ERR_NO_CONVERGENCE and info.ir_iters == 2
+    Ib, nvb, (st, info) = gpu_solve(wl.G, np.tile(wl.V, (103, 1)), wl.geom, **kw)
+    assert st == _lib.XBAR_ERR_NO_CONVERGENCE and info.ir_iters == 2
+    assert np.array_equal(Ib[:B], I) and np.array_equal(nvb[:B], nv)
+
+
+@pytest.mark.parametrize("m,n", [(16, 129), (40, 40), (257, 130)])
+def test_transfer_keeps_the_last_backward_error(m, n):
+    """The backward error of the last solve is still reported after a transfer by unit
+    solves (the first two shapes) and by the block recurrences (the last)."""
+    import torch
+
+    import paper_2410_19993_amd as xb
+    wl = workloads.random_crossbar(m, n, 3, 8850 + m + n)
+    log(f"case backward error, transfer {m}x{n}")
+    with xb.Plan(m, n, 2.5, 2.5, 50.0, 50.0, "fp64", max_batch=max(m, 256), ordering="rows") as p:
+        p.set_diagnostics(True)
+        p.assemble(torch.from_numpy(wl.G).cuda())
+        p.factor()
+        p.solve_batch(torch.from_numpy(wl.V).cuda(), torch.empty((3, 2 * m * n), dtype=torch.float64, device="cuda"))
+        before = p.info()[1].max_backward_err
+        p.transfer()
+        st, info = p.info()
+    assert st == 0 and 0.0 <= before <= 1e-12 and info.max_backward_err == before
