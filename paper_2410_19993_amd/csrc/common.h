@@ -403,4 +403,4 @@ hipError_t xbk_gm_add(const xbk::GmPanel& g, int nv, const double* src, int ld_s
                       hipStream_t s);
 hipError_t xbk_launch_backward_error(const xbk::BackErrArgs& a, hipStream_t s);
 hipError_t xbk_launch_shift_diag(void* E, bool fp32, int m, int n, int n_p, double shift, hipStream_t s);
-hipError_t xbk_launch_reset_diag(unsigned long long* diag, int which, hipStream_t s);
+hipError_t xbk_launch_clear_backward_error(unsigned long long* diag, hipStream_t s);

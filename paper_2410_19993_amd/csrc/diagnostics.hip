@@ -131,12 +131,9 @@ __global__ void shift_diag_kernel(void* E, int m, int n, int n_p, double shift)
     }
 }
 
-__global__ void reset_diag_kernel(unsigned long long* diag, int which)
+__global__ void clear_backward_error_kernel(unsigned long long* diag)
 {
-    if (threadIdx.x == 0) {
-        if (which & 1) diag[kDiagMinPivot] = kPivotKeyInf;
-        if (which & 2) diag[kDiagBackErr] = 0ull;
-    }
+    if (threadIdx.x == 0) diag[kDiagBackErr] = 0ull;
 }
 
 }  // namespace xbk
@@ -159,9 +156,9 @@ hipError_t xbk_launch_shift_diag(void* E, bool fp32, int m, int n, int n_p, doub
     return hipGetLastError();
 }
 
-hipError_t xbk_launch_reset_diag(unsigned long long* diag, int which, hipStream_t s)
+hipError_t xbk_launch_clear_backward_error(unsigned long long* diag, hipStream_t s)
 {
-    hipLaunchKernelGGL(xbk::reset_diag_kernel, dim3(1), dim3(64), 0, s, diag, which);
+    hipLaunchKernelGGL(xbk::clear_backward_error_kernel, dim3(1), dim3(64), 0, s, diag);
     return hipGetLastError();
 }
 

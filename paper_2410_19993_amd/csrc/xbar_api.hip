@@ -1121,7 +1121,7 @@ xbar_status xbar_solve_batch(xbar_plan p, const double* V, int32_t B, double* no
         be.V = V;
         be.node_v = node_v;
         be.diag = p->d.diag;
-        if (xbk_launch_reset_diag(p->d.diag, 2, p->stream) != hipSuccess ||
+        if (xbk_launch_clear_backward_error(p->d.diag, p->stream) != hipSuccess ||
             xbk_launch_backward_error(be, p->stream) != hipSuccess)
             return XBAR_ERR_DEVICE;
         p->backerr_valid = true;
