@@ -754,10 +754,15 @@ __device__ inline GJSlot gj_col_slot(int nb, int nj, int batch, int scol)
 
 // Whether a launch takes column workgroups: they form X once where nb tile workgroups
 // each form it, but walk the column's tiles one after another, so they pay only once the
-// tile workgroups fill the chip four times over.  Factor and sweep of 64 vectors, column
-// against tile workgroups: 256 x 256, 12 crossbars (384 tile workgroups) 21.2 against
-// 18.0 ms, 48 (1536) 29.8 against 28.9; 192 x 192, 40 (720) 12.4 against 11.7, 80 (1440)
-// 17.9 against 19.6.
+// tile workgroups fill the chip four times over.  The line is one for all sizes, at the
+// smallest block's crossing; larger blocks cross later.  64 rows, one vector, ms by column /
+// tile workgroups:
+//   tile workgroups   ~700         ~1000        ~1200        ~1400        ~1600        ~2000
+//   192 columns       4.28 / 4.06  4.97 / 4.78  5.19 / 5.27  5.42 / 5.93  5.82 / 6.52  7.25 / 7.69
+//   256               5.93 / 5.10  6.28 / 5.74  7.17 / 6.59  7.41 / 7.04  7.68 / 7.84  8.17 / 9.06
+//   320               8.27 / 6.69  8.65 / 7.52  8.88 / 8.36  10.2 / 9.00  10.5 / 9.74  11.0 / 11.4
+//   384               10.7 / 8.50  11.1 / 9.63  11.5 / 10.7  11.6 / 10.8  13.5 / 12.1  14.0 / 13.5
+//   512               16.7 / 12.4  17.2 / 12.8  17.5 / 15.4  17.7 / 15.7  17.9 / 15.8  18.8 / 18.6
 inline bool gj_cols(int nj, int nb, int batch) { return nb >= 3 && (int64_t)nj * batch * nb * nb > 1024; }
 
 inline dim3 gj_col_grid(int nj, int nb, int batch)

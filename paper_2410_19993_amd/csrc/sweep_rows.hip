@@ -360,9 +360,11 @@ hipError_t launch_recover_rows(const SweepArgs& a, hipStream_t s)
 // chain has workgroups of its own.  Microseconds a step with node voltages, as launches /
 // chain per workgroup / slab per workgroup: 1024 vectors n = 512 28 / 37 / 72, 320 18.7 /
 // 18.4 / 36, 256 12.5 / 11.7 / 22, 192 9.1 / 9.3 / 18; 1536 vectors 40 / 38, 22 / 18.5,
-// 16.5 / 12.3.  At n_p = 128 a step is too short to be a launch (4.6 / 3.7 / 7.4 with one
+// 16.5 / 12.3.  (The line is one for all sizes: at 64 slabs it costs 256 and 320 columns up
+// to 7%.)  At n_p = 128 a step is too short to be a launch (4.6 / 3.7 / 7.4 with one
 // vector).  Refinement sweeps (float32, with their residual) as launches / slab per
-// workgroup: 2048 vectors 38 / 48 at 512, 1536 vectors 21 / 27 at 320, 17 / 20 at 256.
+// workgroup: 2048 vectors 36 / 44 at 512, 31 / 38 at 448, 24 / 28 at 384, 12.4 / 13.5 at 192;
+// 1536 vectors 21 / 27 at 320, 17 / 20 at 256.
 constexpr int kStepSlabs = 64, kPartSlabs = 128;
 
 template <typename T>

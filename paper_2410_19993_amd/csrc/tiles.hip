@@ -38,9 +38,10 @@
 // eliminated pivot that is not positive, gets NaN currents.  float64 throughout.
 //
 // Bound: the chain of rows; at NP = 64 and 256 vectors a row is 12 us of matrix
-// instructions on one CU (7 of them the forward products).  Measured, 32 crossbars of
-// 128 x 64 with 256 vectors: 2.63 ms (20 us a row; every row eliminated: 5.45); 1000 of
-// 64 x 64: 8.4 ms (21.4); 48 of 32 x 32: 0.24 ms (0.55); 400 of 16 x 16: 0.115 ms (0.18).
+// instructions on one CU (7 of them the forward products).  Measured with 256 vectors, 32
+// crossbars of 128 x 64: 2.60 ms (20 us a row; every row eliminated: 5.44); 1000 of 64 x 64:
+// 5.5 ms (10.8); 48 of 32 x 32: 0.23 ms (0.54); 400 of 16 x 16: 0.116 ms (0.17).  A crossbar
+// of a single row has nothing to gain: 1 x 64 57 us, 50 by the eliminating kernel.
 #include <climits>
 #include <cmath>
 #include <cstdint>

@@ -160,10 +160,12 @@ void tiles_free(xbar_tiles t)
 // A class's expected time alone on the device, in microseconds: its chain of rows, and its
 // flops (factor m n^3, currents-only sweep 2 m n^2 per vector) at 30 TFLOP/s.  The chains'
 // step times are measured: one workgroup 20, 7 or 4 us a row (blocks of 64, 32, 16); the
-// pipeline 24 us a block column of two rows and, in the sweep, 0.042 n_p us a row and side
-// (12 crossbars of 256 x 256 with 256 vectors: 17 ms expected, 18 measured; 24 of
-// 128 x 128: 4.7 and 4.5; 32 of 128 x 64: 2.8 and 2.6).  Flops alone put a chain of many
-// rows that leaves most of the chip idle behind a short one.
+// pipeline 24 us a block column of two rows and, in the sweep, 0.042 n_p us a row and side.
+// Chain and flops overlap, so the sum is 8 to 25% high, alike for all kinds of class, which
+// is what their order needs (256 vectors, expected and measured ms: 12 crossbars of 256 x 256
+// 21.6 and 18.0, 16 of 256 x 128 9.6 and 7.7, 24 of 128 x 128 5.2 and 4.5, 32 of 128 x 64 2.9
+// and 2.6, 1000 of 64 x 64 6.3 and 5.5, 48 of 32 x 32 0.25 and 0.23).  Flops alone put a
+// chain of many rows that leaves most of the chip idle behind a short one.
 double class_time(const xbar_tile_class& c)
 {
     const double m = c.transpose ? c.n : c.m, n = c.transpose ? c.m : c.n, B = c.transpose ? c.n : c.B;

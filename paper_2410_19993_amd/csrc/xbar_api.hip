@@ -211,9 +211,10 @@ bool set_device(xbar_plan p) { return hipSetDevice(p->device) == hipSuccess; }
 // and grows beyond: t = 14, 15, 22, 30, 42, 55, 67, 80 for n_p = 64 .. 512.  Rows:
 // m t(pad(n)); reciprocal: n t(pad(m)).  With it, among the wide shapes up to 256 x 512
 // the reciprocal wins at 128 x 512 and 256 x 512 and loses at every smaller or narrower
-// one, as the measurements did.  (They were taken with three launches a row at every
-// size; a row of a small batch is now 1 to 28 us.  The line stays where callers know it:
-// the choice sets a plan's block size, and at large batches the flops decide alike.)
+// one, as the measurements did.  They were taken with three launches a row at every size; a
+// row of a small batch is now 1 to 28 us, and with one vector the other ordering is the
+// faster at 32 x 256 (rows 1.01 ms, smaller side 0.44) and 128 x 512 (4.81 and 5.74).  The
+// choice has not been measured again at larger batches and stays as it was.
 double row_us(int n)
 {
     const int n_p = 64 * ((n + 63) / 64);
